@@ -1,29 +1,32 @@
 // Block-sparse attention forward (Eq. 7, Section 5.3) and its dense variant.
 //
-// Work decomposition.  One work-group per (batch*head, query block of BLK
-// rows, key range), launched so that the eight XCDs stream disjoint key ranges
-// of the same head (see the work-item decode below).  The work-group has one
-// wavefront per 32-row query slice (two for 64-row blocks, four for 128-row
-// blocks), and every wave takes the whole of each key tile, so no key is ever
-// split between waves.  Keys come in tiles of KB = BLK / 2 (32 keys for 64-row
-// blocks, 64 for 128-row blocks; a key block is two tiles), which sizes the LDS
-// ring at 40 KB (80 KB) per work-group at D = 128: four (two) work-groups per
-// CU, two waves per SIMD, each under 256 VGPRs.
+// Work decomposition.  One work-group per (batch*head, key range, query group).
+// A query group of the sparse call is one query block of BLK rows; the dense
+// call, whose rows all see the same keys, takes 128 rows whatever the block
+// size, so that each K/V byte loaded feeds twice (b = 64) the queries.  A
+// work-group has one wavefront per 32-row query slice, and every wave takes the
+// whole of each 32-key tile, so no key is ever split between waves and a row's
+// result does not depend on how many waves share its tiles.  Two waves per SIMD
+// at D = 128 (under 256 VGPRs), three at D = 64 (under 168).
 //
-// Per tile of the query block's ascending key-block list:
-//   * K and V tiles (KB x D) go from global memory straight into LDS
+// Order of the work (XCDs and L2).  Work-groups go round-robin over the eight
+// XCDs.  The id decodes so that each XCD runs the query groups of one (head, key
+// range) pair after the other, and its L2 holds one range of the head's K/V.
+//
+// Per tile of the query block's key-block list, a three-stage pipeline: step t
+// runs the scores of tile t + 1, the softmax of tile t and P V of tile t - 1.
+//   * K and V tiles (32 x D) go from global memory straight into LDS
 //     (buffer_load ... lds, 1 KB per wave instruction, coalesced), with no
-//     VGPR staging.  LDS holds a ring of three K tiles and two V tiles; each
-//     step has two barrier phases (scores, then P V), and each phase's barrier
-//     frees the slot the next loads go into;
+//     VGPR staging.  LDS holds two K tiles and two V tiles; each tile has one
+//     and a half steps to land;
 //   * S^T = K Q^T on v_mfma_f32_32x32x16_bf16 (fp32 accumulate).  The
 //     transpose leaves each lane holding 16 keys of ONE query column -- exactly
 //     the B-operand layout P^T needs -- so the softmax state is lane-local up to
-//     one cross-half (lane l <-> l+32) max per step (v_permlane32_swap);
+//     one cross-half (lane l <-> l+32) max per refresh (v_permlane32_swap);
 //   * online softmax in the log2 domain: the scale is folded into one FMA, the
 //     exponential is the bare v_exp_f32, and the running maximum is not taken
 //     per tile: P is formed against the current one, and only when some lane's
-//     sum of a sub-tile's P exceeds 2^8 (so that some p might) is the tile's
+//     sum of a tile's P exceeds 2^8 (so that some p might) is the tile's
 //     max taken, O and the sums rescaled by a power of two, and P formed
 //     again -- nearly never after the first tiles;
 //   * O^T += V^T P^T on the same MFMA (P rounded to bf16 once).  The V^T
@@ -31,8 +34,25 @@
 //     transpose read ds_read_b64_tr_b16 (in each 16-lane group, source lane s
 //     points at V[r0 + s/4][4 (c0 + s%4)], and lane j receives
 //     V[r0 .. r0+3][4 c0 + j]: 4 keys of one d column).
+// None of a step's MFMAs waits for the step's softmax or for an LDS read of the
+// same half: the operands of each half are read during the half before.  Every
+// MFMA is followed by its share of the softmax (at D = 128 one exponential, one
+// FMA, one add and half a pack), which issues under it: a 32x32x16 MFMA takes
+// 32 cycles, an FMA 2.7 and an exponential 8.
+// The row sum of the bf16 P is taken by v_mfma_f32_4x4x4_16b_bf16 against ones
+// (each lane's four values summed in 8 cycles).  v_dot2_f32_bf16, which sums
+// two, runs on the matrix pipe as well but holds it for about 20 cycles: eight
+// of them per tile cost 10% of the kernel (26.3 ms without them against 29.1 at
+// 25,920 queries, dense).
 // O = O^T / l in bf16 with l the row sum of the bf16-rounded P, and
 // lse = ln2*(m + log2 le) with le the row sum of the unrounded fp32 p.
+//
+// What bounds it (24 heads, D = 128, one box): the dense call runs at 1.17
+// PFLOP/s against 1.28 for a large library GEMM; the matrix cores are busy 63%
+// of the cycles at 1.65 GHz, the clock the chip holds under this load.  The sparse
+// call at b = 64 streams 64 KB of K/V per 64 x 128 tile pair from L2, as many
+// texture-path clocks as MFMA clocks, and without those loads would take 25.6
+// instead of 33.4 ms.
 //
 // MFMA layouts (v_mfma_f32_32x32x16_bf16, lane l, h = l / 32):
 //   A[m][k]: m = l % 32, k = 8h + i (i = 0..7 of the lane's bf16x8)
@@ -53,12 +73,13 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
-template <int D, int BLK>
+// A 32-key step with two waves per SIMD; 64-key tiles need more than 256 VGPRs in
+// this pipeline.
+template <int D, int BLK, int NWAVES>
 struct AttnCfg {
-  static constexpr int KB = BLK / 2;          // keys per K/V tile
+  static constexpr int KB = 32;               // keys per K/V tile
   static constexpr int SUB = BLK / KB;        // tiles per key block (list entry)
-  static constexpr int NQS = BLK / 32;        // 32-row query slices
-  static constexpr int NW = NQS;              // waves: one per query slice
+  static constexpr int NW = NWAVES;           // waves: one per 32-row query slice
   static constexpr int NT = 64 * NW;          // threads
   static constexpr int KT = KB / 32;          // 32-key sub-tiles per step
   static constexpr int DS = D / 16;           // MFMA k-steps over D
@@ -71,6 +92,7 @@ struct AttnCfg {
   static constexpr int RPD = 1024 / RB;       // rows per direct-to-LDS wave load (64 lanes x 16 B)
   static constexpr int DPW = TILE_BYTES / 1024 / NW;  // direct loads per wave and tile
   static_assert(DPW * NW * 1024 == TILE_BYTES, "tile split over the waves");
+  static constexpr int NK = 2, NV = 2;        // LDS ring: K and V tiles held
   static_assert(KT * 32 == KB, "32-key sub-tiles");
   static_assert(SUB * KB == BLK, "whole tiles per key block");
 };
@@ -82,14 +104,12 @@ struct AttnCfg {
 //     physical chunk = c ^ (r / RPB mod CPR)
 //   V (ds_read_b64_tr_b16, 32 lanes per pass: 4 consecutive rows x 4 chunks):
 //     physical chunk = c ^ ((r / RPB mod 4) * 4 mod CPR)
-template <int D, int BLK>
+template <class C>
 __device__ __forceinline__ int k_swz(int r) {
-  using C = AttnCfg<D, BLK>;
   return (r / C::RPB) % C::CPR;
 }
-template <int D, int BLK>
+template <class C>
 __device__ __forceinline__ int v_swz(int r) {
-  using C = AttnCfg<D, BLK>;
   return (((r / C::RPB) & 3) << 2) & (C::CPR - 1);
 }
 
@@ -185,43 +205,42 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-template <int D, int BLK, bool DENSE, bool SPLIT>
-__global__ __launch_bounds__(BLK * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int D, int BLK, int NW, bool DENSE, bool SPLIT>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(attn_waves_per_simd(D), attn_waves_per_simd(D))))
 void attn_fwd_kernel(AttnArgs a) {
-  using C = AttnCfg<D, BLK>;
-  // Ring of three K tiles and two V tiles.  Step t reads K of tile t+1 (the
-  // scores one step ahead) and V of tile t; at its start it issues the
-  // direct-to-LDS loads of V of tile t+1 and K of tile t+3 into the slots that
-  // the previous step released.  K(j) lives in slot j mod 3, V(j) in j mod 2.
-  __shared__ __attribute__((aligned(1024))) uint16_t ks0[C::TILE], ks1[C::TILE], ks2[C::TILE];
-  __shared__ __attribute__((aligned(1024))) uint16_t vs0[C::TILE], vs1[C::TILE];
+  using C = AttnCfg<D, BLK, NW>;
+  static_assert(DENSE || 32 * NW == BLK, "a sparse work-group is one query block");
+  __shared__ __attribute__((aligned(1024))) uint16_t ks[C::NK][C::TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t vs[C::NV][C::TILE];
 
-  // Work item.  Work-groups are dispatched round-robin over the eight XCDs, so
-  // with the key-range split the work-group id decodes as
-  //   id = ((bh * S + s) * n_q + qb) * 8 + x,  range r = 8 s + x,  S = n_splits / 8:
-  // XCD x runs range x of every query block of head bh, then range 8 + x, ...,
-  // and its L2 holds one range of the head's K/V at a time.
-  int split = 0;
-  int64_t work = blockIdx.x;
-  if constexpr (SPLIT) {
-    const int S = a.n_splits / 8;
-    const int64_t x = blockIdx.x % 8, rest = blockIdx.x / 8;
-    const int64_t qbi = rest % a.n_q, rest2 = rest / a.n_q;
-    split = (int)((rest2 % S) * 8 + x);
-    work = (rest2 / S) * a.n_q + qbi;
+  // Work item: query group qg of the (head, range) pair bh * n_splits + split.
+  // Eight pairs at a time run side by side, pair 8 i + x on XCD x; the query
+  // groups of the last (fewer than eight) pairs are dealt out to the XCDs in
+  // eight equal consecutive shares.
+  const int n_g = DENSE ? (int)((a.lq + 32 * NW - 1) / (32 * NW)) : a.n_q;  // query groups per head
+  const int n_ranges = SPLIT ? a.n_splits : 1;
+  const int64_t pairs = (int64_t)a.bh * n_ranges, whole = pairs / 8 * 8;
+  int64_t pair, id = blockIdx.x;
+  int qg;
+  if (id < whole * n_g) {
+    pair = id / 8 / n_g * 8 + id % 8;
+    qg = (int)(id / 8 % n_g);
+  } else {
+    id = xcd_linear(id - whole * n_g, (pairs - whole) * n_g);
+    pair = whole + id / n_g;
+    qg = (int)(id % n_g);
   }
-  const int64_t bh = work / a.n_q;
-  const int qb = (int)(work % a.n_q);
-  const int blk_lo = SPLIT ? (int)((int64_t)split * a.n_k / a.n_splits) : 0;
-  const int blk_hi = SPLIT ? (int)((int64_t)(split + 1) * a.n_k / a.n_splits) : a.n_k;
+  const int64_t bh = pair / n_ranges;
+  const int split = (int)(pair % n_ranges);
+  const int blk_lo = (int)((int64_t)split * a.n_k / n_ranges);
+  const int blk_hi = (int)((int64_t)(split + 1) * a.n_k / n_ranges);
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int l32 = lane % 32, hh = lane / 32;
-  const int qs = wave;  // query slice
 
   // ---- Q fragment (B operand of S^T = K Q^T): Q[q][16 s + 8 hh .. +7]
-  const int64_t q_row = (int64_t)qb * BLK + qs * 32 + l32;
+  const int64_t q_row = (int64_t)qg * (32 * NW) + wave * 32 + l32;
   const bool q_ok = q_row < a.lq;
   const uint16_t* qp = a.q + (bh * a.lq + (q_ok ? q_row : 0)) * D;
   bf16x8 qf[C::DS];
@@ -240,7 +259,7 @@ void attn_fwd_kernel(AttnArgs a) {
     pos_lo = blk_lo;
     cnt = blk_hi - blk_lo;
   } else {
-    const int64_t r = bh * a.n_q + qb;
+    const int64_t r = bh * a.n_q + qg;
     int nblk = a.kv_num_blocks[r];
     nblk = nblk < 0 ? 0 : (nblk > a.stride ? a.stride : nblk);
     list = a.kv_indices + r * a.stride;
@@ -269,16 +288,17 @@ void attn_fwd_kernel(AttnArgs a) {
 
   // ---- the key tiles of the item.  Tile j (KB keys) is tile j % SUB of the key
   // block at list position pos_lo + j / SUB.  The entries are held 64 at a time
-  // in a VGPR (lane i: entry lbase + i) and picked out with v_readlane, so the
-  // loop issues no memory load of its own except one batch load per 64
-  // entries.  j >= cnt * SUB, and an entry outside [blk_lo, blk_hi) -- only
-  // possible in a list that is not ascending --, give -1: a tile that is
-  // loaded as zeros and fully masked.
+  // in a VGPR (lane i: entry lbase + i, as its first tile) and picked out with
+  // v_readlane, so the loop issues no memory load of its own except one batch
+  // load per 64 entries.  j >= cnt * SUB, and an entry outside [blk_lo, blk_hi)
+  // -- only possible in a list that is not ascending --, give a negative tile:
+  // one that is loaded as zeros and fully masked.
   int lreg = -1, lbase = 0;
   auto load_batch = [&](int base) {
     lbase = base;
     if constexpr (!DENSE) {
-      lreg = base + lane < cnt ? list[pos_lo + base + lane] : -1;
+      const int b = base + lane < cnt ? list[pos_lo + base + lane] : -1;
+      lreg = (b >= blk_lo && b < blk_hi) ? b * C::SUB : -C::SUB;
       // consume the load here, so that its wait stays on this rare path and is
       // not merged into the common path of the loop
       asm volatile("; list batch %0" ::"v"(lreg));
@@ -286,19 +306,14 @@ void attn_fwd_kernel(AttnArgs a) {
   };
   const int ntiles = cnt * C::SUB;
   auto fetch = [&](int j) -> int {
-    if (j >= ntiles) return -1;
-    const int e = j / C::SUB, sub = j % C::SUB;
     if constexpr (DENSE) {
-      int kt = (blk_lo + e) * C::SUB + sub;
-      // At 128-row blocks the tile index is hidden from the compiler, which
-      // would otherwise precompute the addresses of all six unrolled steps and
-      // spill registers to scratch.
-      if constexpr (BLK == 128) asm volatile("" : "+s"(kt));
-      return kt;
+      // (opaque to the compiler, which would otherwise keep addresses of several
+      // steps and spill registers to scratch)
+      return __builtin_amdgcn_readfirstlane(j < ntiles ? blk_lo * C::SUB + j : -1);
     } else {
+      const int e = j / C::SUB, sub = j % C::SUB;
       if (e >= lbase + 64) load_batch(lbase + 64);
-      const int b = __builtin_amdgcn_readlane(lreg, e - lbase);
-      return (b >= blk_lo && b < blk_hi) ? b * C::SUB + sub : -1;
+      return __builtin_amdgcn_readlane(lreg, e - lbase) + sub;
     }
   };
 
@@ -329,17 +344,18 @@ void attn_fwd_kernel(AttnArgs a) {
   uint32_t kdma, vdma;
   {
     const int row = C::RPD * C::DPW * wave + lane / C::CPR, pos = lane % C::CPR;
-    kdma = (uint32_t)(row * C::RB + 16 * (pos ^ k_swz<D, BLK>(row)));
-    vdma = (uint32_t)(row * C::RB + 16 * (pos ^ v_swz<D, BLK>(row)));
+    kdma = (uint32_t)(row * C::RB + 16 * (pos ^ k_swz<C>(row)));
+    vdma = (uint32_t)(row * C::RB + 16 * (pos ^ v_swz<C>(row)));
   }
   const uint16_t* const kbase = a.k + bh * a.lk * D;
   const uint16_t* const vbase = a.v + bh * a.lk * D;
-  // tiles are KB keys; the last one may be partial, and with SUB > 1 the last
-  // tiles of a partial key block may lie wholly past Lk (0 bytes)
-  const int n_kt = (int)((a.lk + C::KB - 1) / C::KB);
-  const uint32_t last_bytes = (uint32_t)(a.lk - (int64_t)(n_kt - 1) * C::KB) * (uint32_t)C::RB;
+  // Tiles [0, n_whole) lie wholly below Lk; tile n_whole holds the remaining
+  // keys (none if Lk is a whole number of tiles); later tiles and -1 (as
+  // unsigned) hold none.
+  const uint32_t n_whole = (uint32_t)(a.lk / C::KB);
+  const uint32_t last_bytes = (uint32_t)(a.lk % C::KB) * (uint32_t)C::RB;
   auto tile_bytes = [&](int kt) -> uint32_t {
-    return (kt < 0 || kt >= n_kt) ? 0u : (kt == n_kt - 1 ? last_bytes : (uint32_t)C::TILE_BYTES);
+    return (uint32_t)kt < n_whole ? (uint32_t)C::TILE_BYTES : ((uint32_t)kt == n_whole ? last_bytes : 0u);
   };
   auto dma = [&](const uint16_t* base, int blk, uint16_t* slot, uint32_t off0, uint32_t step) {
     const i32x4 rs = raw_rsrc(base + (int64_t)(blk < 0 ? 0 : blk) * C::TILE, tile_bytes(blk));
@@ -355,7 +371,7 @@ void attn_fwd_kernel(AttnArgs a) {
   {
     const int r = l32;
 #pragma unroll
-    for (int s = 0; s < C::DS; ++s) koff[s] = (uint32_t)(r * C::RB + 16 * ((2 * s + hh) ^ k_swz<D, BLK>(r)));
+    for (int s = 0; s < C::DS; ++s) koff[s] = (uint32_t)(r * C::RB + 16 * ((2 * s + hh) ^ k_swz<C>(r)));
   }
   // V^T operand through the transpose read: in each 16-lane group g, source lane
   // sl points at row R = 4 hh + sl / 4 (+ 32 kt + 16 half + 8 for the
@@ -369,53 +385,47 @@ void attn_fwd_kernel(AttnArgs a) {
 #pragma unroll
     for (int t = 0; t < C::DT; ++t) {
       const int c = 4 * t + 2 * (grp & 1) + ((sl & 3) >> 1);
-      voff[t] = (uint32_t)(r * C::RB + 16 * (c ^ v_swz<D, BLK>(r)) + 8 * (sl & 1));
+      voff[t] = (uint32_t)(r * C::RB + 16 * (c ^ v_swz<C>(r)) + 8 * (sl & 1));
     }
   }
-  auto kslot = [&](auto i) -> uint16_t* {
-    constexpr int I = decltype(i)::value;
-    if constexpr (I == 0) return ks0;
-    else if constexpr (I == 1) return ks1;
-    else return ks2;
-  };
-  auto vslot = [&](auto i) -> uint16_t* {
-    constexpr int I = decltype(i)::value;
-    if constexpr (I == 0) return vs0;
-    else return vs1;
-  };
   auto lds_u4 = [](const uint16_t* slot, uint32_t byte_off) -> uint4 {
     return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(slot) + byte_off);
   };
 
   const float sl2 = a.scale_log2;
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+  const s16x4 one4 = {0x3f80, 0x3f80, 0x3f80, 0x3f80};  // bf16 1.0
 
-  // keys >= Lk of a partial last block, and every key of a -1 tile, get -inf
-  auto mask_tile = [&](f32x16* acc, int blk) {
-    const int64_t key0 = (int64_t)blk * C::KB;
-    if (blk < 0 || key0 + C::KB > a.lk) {
+  // keys >= Lk of a partial last tile, and every key of a tile past it or of a
+  // negative one, get -inf (element e of the lane is key 8 (e / 4) + 4 hh + e % 4
+  // of its sub-tile, compared against one per-lane count of visible keys)
+  auto mask_tile = [&](f32x16* acc, int kt_id) {
+    const int64_t left = kt_id < 0 ? 0 : a.lk - (int64_t)kt_id * C::KB;
+    const int vis = (int)(left < 0 ? 0 : (left > C::KB ? C::KB : left)) - 4 * hh;
 #pragma unroll
-      for (int kt = 0; kt < C::KT; ++kt)
+    for (int kt = 0; kt < C::KT; ++kt)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int key = kt * 32 + 8 * (e / 4) + 4 * hh + (e % 4);
-          if (blk < 0 || key0 + key >= a.lk) acc[kt][e] = -INFINITY;
-        }
-    }
+      for (int e = 0; e < 16; ++e)
+        if (kt * 32 + 8 * (e / 4) + (e % 4) >= vis) acc[kt][e] = -INFINITY;
   };
-  int b1 = -1, b2 = -1, b3 = -1, b4 = -1;  // blocks of tiles t+1 .. t+4
   f32x16 acc_s[C::KT];                     // S^T of tile t
+  uint32_t pp[C::KT][8];                   // bf16 pairs of P^T of tile t-1
+  uint4 kf[C::KT][C::DS];                  // K operands of tile t+1
 
-  // S^T of one K tile (LDS slot ks) into acc
-  auto scores = [&](const uint16_t* ks, f32x16* acc) {
+  auto read_k = [&](const uint16_t* kt_lds) {
+#pragma unroll
+    for (int kt = 0; kt < C::KT; ++kt)
+#pragma unroll
+      for (int s = 0; s < C::DS; ++s) kf[kt][s] = lds_u4(kt_lds, koff[s] + kt * 32 * C::RB);
+  };
+  // S^T of the tile whose K operands are in kf
+  auto scores = [&](f32x16* acc) {
 #pragma unroll
     for (int kt = 0; kt < C::KT; ++kt) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[kt][e] = 0.f;
 #pragma unroll
       for (int s = 0; s < C::DS; ++s)
-        acc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-            __builtin_bit_cast(bf16x8, lds_u4(ks, koff[s] + kt * 32 * C::RB)), qf[s], acc[kt], 0, 0, 0);
+        acc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[kt][s]), qf[s], acc[kt], 0, 0, 0);
     }
   };
   // the tile's max logit (log2 domain) of the lane's query over both lane halves
@@ -427,236 +437,213 @@ void attn_fwd_kernel(AttnArgs a) {
       for (int e = 0; e < 16; ++e) mx = fmaxf(mx, acc[kt][e]);
     return mx;
   };
-  // tiles [0, n_whole) lie wholly below Lk; -1 (as unsigned) and the rest need the mask
-  const uint32_t n_whole = (uint32_t)(a.lk / C::KB);
   auto needs_mask = [&](int blk) { return (uint32_t)blk >= n_whole; };
 
+  // V^T operands of one tile: step m = (2 kt + half) DT + dt.
+  // accumulators a = 8 half + i of sub-tile kt hold keys
+  //   base + 4 hh + i (i = 0..3) and base + 8 + 4 hh + (i - 4) (i = 4..7),
+  // base = 32 kt + 16 half; the two transpose reads fetch the
+  // same keys of V for d = 32 t + l % 32.
+  constexpr int VM = 2 * C::KT * C::DT;
+  auto read_v = [&](const uint16_t* vt, int m) -> s16x8 {
+    const uint16_t* vp = reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(vt) + voff[m % C::DT] +
+                                                           16 * (m / C::DT) * C::RB);
+    const s16x4 v0 = lds_read_tr(vp);
+    const s16x4 v1 = lds_read_tr(vp + 8 * D);
+    return __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  // O^T += V^T P^T of one tile, MFMA m over a 16-key k-step
+  auto pv = [&](int m, s16x8 v, const uint32_t (&pk)[C::KT][8]) {
+    const int kt = m / C::DT / 2, half = m / C::DT % 2, dt = m % C::DT;
+    uint4 pu;
+    pu.x = pk[kt][4 * half + 0];
+    pu.y = pk[kt][4 * half + 1];
+    pu.z = pk[kt][4 * half + 2];
+    pu.w = pk[kt][4 * half + 3];
+    acc_o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, pu),
+                                                        acc_o[dt], 0, 0, 0);
+  };
+
   if (cnt > 0) {
-    // ---- prologue.  The loads follow the order of the steady state (K(j+4)
-    // after the first barrier of step j, V(j+2) after the second), so that the
-    // vmcnt thresholds of the step hold from the first step on.
+    // ---- prologue: S of tile 0, the K operands of tile 1 in registers, and the
+    // loads of K(2), V(0), K(3) in the order in which the steps wait for them.
     load_batch(0);
     const int b0 = fetch(0);
-    b1 = fetch(1);
-    b2 = fetch(2);
-    b3 = fetch(3);
-    b4 = fetch(4);
-    dma(kbase, b0, ks0, kdma, 64u);
-    dma(kbase, b1, ks1, kdma, 64u);
-    dma(kbase, b2, ks2, kdma, 64u);
-    dma(vbase, b0, vs0, vdma, 0u);
-    wait_vmcnt<3 * C::DPW>();  // K(0)
+    int b1 = fetch(1), b2 = fetch(2), b3 = fetch(3);  // tiles t+1 .. t+3
+    dma(vbase, -1, vs[1], vdma, 0u);  // zeros: "tile -1" of the first step's P V
+#pragma unroll
+    for (int kt = 0; kt < C::KT; ++kt)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pp[kt][i] = 0u;
+    dma(kbase, b0, ks[0], kdma, 64u);
+    dma(kbase, b1, ks[1], kdma, 64u);
+    wait_vmcnt<0>();
     __syncthreads();
-    scores(ks0, acc_s);
+    read_k(ks[0]);
+    scores(acc_s);
     if (needs_mask(b0)) mask_tile(acc_s, b0);
     m_run = half_swap_max(tile_max(acc_s)) * sl2;  // O and the sums are still zero
-    __syncthreads();  // K slot 0 is free
-    dma(kbase, b3, ks0, kdma, 64u);
-    wait_vmcnt<3 * C::DPW>();  // K(1)
-    __syncthreads();
-    dma(vbase, b1, vs1, vdma, 0u);
+    read_k(ks[1]);
+    __syncthreads();  // both K slots are free
+    dma(kbase, b2, ks[0], kdma, 64u);
+    dma(vbase, b0, vs[0], vdma, 0u);
+    dma(kbase, b3, ks[1], kdma, 64u);
 
-    // One step (T = t mod 6 fixes the slots), in two phases:
-    //   A: the scores of tile t+1 on the matrix cores while the exponentials of
-    //      tile t run; then V(t) is waited for, a barrier releases K slot
-    //      (t+1) % 3, and K(t+4) is loaded into it (it has 2.5 steps to land);
-    //   B: O += P V of tile t; then K(t+2) is waited for, a barrier releases V
-    //      slot t % 2, and V(t+2) is loaded into it (1.5 steps to land).
-    // Apart from the rare exact path of phase A, the phases are branch-free,
-    // and sched_group_barrier interleaves their MFMAs with their VALU work so
-    // that the latter hides under the matrix cores.
+    // One step (T = t mod 2 fixes the slots; tile j's K and V are in slot j % 2)
+    // in two phases:
+    //   A: S of tile t+1 (K operands in registers) while V(t-1) is read; then
+    //      K(t+2) is waited for, a barrier frees V(t-1)'s slot for V(t+1);
+    //   B: O += P V of tile t-1 while K(t+2) is read; then V(t) is waited for, a
+    //      barrier frees K(t+2)'s slot for K(t+4).
+    // The softmax of tile t is spread evenly over the MFMAs of both.  A tile's
+    // loads have one and a half steps to land, and each wait leaves the two
+    // tiles issued after it outstanding.
     int t = 0;
     auto step = [&](auto tc) {
       constexpr int T = decltype(tc)::value;
-      constexpr int KS = (T + 1) % 3, VS = T % 2;
-      uint16_t* const kr = kslot(std::integral_constant<int, KS>{});
-      uint16_t* const vr = vslot(std::integral_constant<int, VS>{});
+      uint16_t* const kr = ks[T % 2];        // K(t+2)
+      uint16_t* const vr = vs[(T + 1) % 2];  // V(t-1)
+      constexpr int MA = C::DS * C::KT;      // MFMAs of phase A
+      constexpr int NE = 16 * C::KT;         // elements of S per lane
+      constexpr int EPM = NE / (MA + VM);    // elements per MFMA
+      static_assert(MA == VM && EPM * (MA + VM) == NE, "softmax spread over the MFMAs");
 
-      // ---- phase A, per 32-key sub-tile kt: the K reads and score MFMAs of
-      // tile t+1 interleaved with the exponentials of sub-tile kt of tile t.
-      // The running max is only refreshed when a sub-tile could break the
-      // bound p <= 2^8: a lane's sum of the sub-tile's P stays <= 2^8 whenever
-      // every p does, so a larger (or non-finite) sum in any lane sends the
-      // wave to the exact path -- the sub-tile's max, a rescale of O and both
-      // sums to it, and the sub-tile's P again (then p <= 1 there).
       f32x16 acc_n[C::KT];
-      uint32_t pk[C::KT][8];  // bf16 pairs of P^T, per 32-key sub-tile
-      float pf[C::KT][16];    // the same p in fp32, summed for lse in phase B (one sub-tile per step)
+      s16x8 vf[VM];
+      uint32_t pk[C::KT][8];  // bf16 pairs of P^T of tile t
+      float se = 0.f;         // row sum of the tile's fp32 p (the lane's keys)
+      // exp2 offset -m; +inf for a query that has seen no key yet, which makes
+      // the sum non-finite and takes the exact path
+      const float neg_m = m_run == -INFINITY ? INFINITY : -m_run;
+      float x[NE], p[NE];
+      f32x4 st4 = {0.f, 0.f, 0.f, 0.f};  // row sum of the tile's bf16 P, in all four
+      auto row_sum = [&](int i) {        // adds pairs i - 1 and i (i odd) of P
+        const uint2 u = make_uint2(pk[i / 8][i % 8 - 1], pk[i / 8][i % 8]);
+        st4 = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(one4, __builtin_bit_cast(s16x4, u), st4, 0, 0, 0);
+      };
+      auto logit = [&](int e) { x[e] = fmaf(acc_s[e / 16][e % 16], sl2, neg_m); };
+      auto prob = [&](int e) { p[e] = __builtin_amdgcn_exp2f(x[e]); };
+      // The softmax work that follows MFMA number e / EPM: each stage works one
+      // element behind the stage before, so that no instruction waits for the
+      // one ahead of it.
+      auto element = [&](int e) {
+        if (e + 2 < NE) logit(e + 2);
+        if (e + 1 < NE) prob(e + 1);
+        se = e == 0 ? p[0] : se + p[e];
+        if (e % 2 == 1)
+          pk[e / 16][e % 16 / 2] = pack2_bf16(p[e - 1], p[e]);
+        else if (e >= 4 && e % 4 == 0)
+          row_sum(e / 2 - 1);
+        // holds the work here (it would otherwise sink to its uses)
+        if (e + 2 < NE) asm volatile("" : "+v"(x[e + 2]));
+        if (e + 1 < NE) asm volatile("" : "+v"(p[e + 1]));
+        asm volatile("" : "+v"(se));
+        if (e % 2 == 1) asm volatile("" : "+v"(pk[e / 16][e % 16 / 2]));
+      };
+      logit(0);
+      logit(1);
+      prob(0);
+      __builtin_amdgcn_sched_barrier(0);
+
+      // ---- phase A
 #pragma unroll
-      for (int kt = 0; kt < C::KT; ++kt) {
-        // exp2 offset -m; +inf for a query that has seen no key yet, which makes
-        // the sum non-finite and takes the exact path
-        const float neg_m = m_run == -INFINITY ? INFINITY : -m_run;
-        float st = 0.f;  // row sum of the sub-tile's bf16 P (the lane's keys)
-        float se = 0.f;  // with two sub-tiles per step: row sum of its fp32 p
-        auto exps = [&](float off) {
+      for (int i = 0; i < MA; ++i) {
+        const int kt = i / C::DS, s = i % C::DS;
+        if (s == 0)
 #pragma unroll
-          for (int e = 0; e < 16; e += 2) {
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(acc_s[kt][e], sl2, off));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(acc_s[kt][e + 1], sl2, off));
-            pk[kt][e / 2] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p0, p1}, bf16x2));
-            st = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk[kt][e / 2]), ones, st, false);
-            if constexpr (C::KT == 1) {
-              pf[kt][e] = p0;
-              pf[kt][e + 1] = p1;
-            } else {
-              se += p0 + p1;
-            }
-          }
-        };
-        uint4 kf[C::DS];
+          for (int e = 0; e < 16; ++e) acc_n[kt][e] = 0.f;
+        acc_n[kt] =
+            __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[kt][s]), qf[s], acc_n[kt], 0, 0, 0);
+        vf[i] = read_v(vr, i);
 #pragma unroll
-        for (int s = 0; s < C::DS; ++s) kf[s] = lds_u4(kr, koff[s] + kt * 32 * C::RB);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc_n[kt][e] = 0.f;
-#pragma unroll
-        for (int s = 0; s < C::DS; ++s)
-          acc_n[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[s]), qf[s],
-                                                              acc_n[kt], 0, 0, 0);
-        exps(neg_m);
-        if constexpr (C::DS == 8) {
-          // the K reads in groups of RG, then 8 x (score MFMA + VA VALU of the
-          // exponentials and row sums); with two sub-tiles per step (64-key
-          // tiles) the K reads go four at a time and the fp32 row sum is
-          // taken here: both keep the wave under 256 VGPRs without spills
-          constexpr int RG = C::KT == 1 ? 8 : 4;  // K reads per group
-          constexpr int VA = C::KT == 1 ? 6 : 8;  // VALU per score MFMA
-#pragma unroll
-          for (int g = 0; g < 8 / RG; ++g) {
-            __builtin_amdgcn_sched_group_barrier(0x100, RG, 0);
-#pragma unroll
-            for (int i = 0; i < RG; ++i) {
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-              __builtin_amdgcn_sched_group_barrier(0x002, VA, 0);
-            }
-          }
-        }
+        for (int e = 0; e < EPM; ++e) element(EPM * i + e);
         __builtin_amdgcn_sched_barrier(0);
-        if (__builtin_amdgcn_ballot_w64(!(st <= 256.f))) {
-          float mx = -INFINITY;
-#pragma unroll
-          for (int e = 0; e < 16; ++e) mx = fmaxf(mx, acc_s[kt][e]);
-          mx = half_swap_max(mx) * sl2;
-          if (mx > m_run) {
-            // the max moves up by a whole number of binades (to >= mx), so the
-            // rescale is exact, also on the bf16 P of the step's earlier
-            // sub-tiles, which are not yet in O but already in l and le.  A
-            // jump past 2^128 (or the first key) drops the old terms, which
-            // are then below 2^-120 of the new ones.
-            float alpha = 0.f;
-            const float dm = mx - m_run;
-            if (dm > 128.f) {
-              m_run = mx;
-            } else {
-              const float k = ceilf(dm);
-              alpha = __builtin_amdgcn_ldexpf(1.f, -(int)k);
-              m_run += k;
-            }
-            l_run *= alpha;
-            le_run *= alpha;
-#pragma unroll
-            for (int d = 0; d < C::DT; ++d)
-#pragma unroll
-              for (int e = 0; e < 16; ++e) acc_o[d][e] *= alpha;
-#pragma unroll
-            for (int j = 0; j < kt; ++j)
-#pragma unroll
-              for (int i = 0; i < 8; ++i)
-                pk[j][i] = pack2_bf16(__uint_as_float(pk[j][i] << 16) * alpha,
-                                      __uint_as_float(pk[j][i] & 0xffff0000u) * alpha);
-          }
-          st = 0.f;
-          se = 0.f;
-          exps(m_run == -INFINITY ? 0.f : -m_run);
-        }
-        l_run += st;
-        if constexpr (C::KT != 1) le_run += se;
       }
+      wait_vmcnt<2 * C::DPW>();  // K(t+2)
+      __syncthreads();
+      dma(vbase, b1, vr, vdma, 0u);  // V(t+1)
+
+      // ---- phase B
+#pragma unroll
+      for (int i = 0; i < VM; ++i) {
+        pv(i, vf[i], pp);
+        kf[i / C::DS][i % C::DS] = lds_u4(kr, koff[i % C::DS] + i / C::DS * 32 * C::RB);
+#pragma unroll
+        for (int e = 0; e < EPM; ++e) element(EPM * (MA + i) + e);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      row_sum(NE / 2 - 1);
+      float st = st4[0];
+      const int b4 = fetch(t + 4);
       wait_vmcnt<2 * C::DPW>();  // V(t)
       __syncthreads();
-      dma(kbase, b4, kr, kdma, 64u);
+      dma(kbase, b4, kr, kdma, 64u);  // K(t+4)
 
-      // ---- phase B: O^T += V^T P^T over 16-key k-steps
-#pragma unroll
-      for (int kt = 0; kt < C::KT; ++kt)
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          // accumulators a = 8 half + i of sub-tile kt hold keys
-          //   base + 4 hh + i (i = 0..3) and base + 8 + 4 hh + (i - 4) (i = 4..7),
-          // base = 32 kt + 16 half; the two transpose reads fetch the
-          // same keys of V for d = 32 t + l % 32.
-          uint4 pu;
-          pu.x = pk[kt][4 * half + 0];
-          pu.y = pk[kt][4 * half + 1];
-          pu.z = pk[kt][4 * half + 2];
-          pu.w = pk[kt][4 * half + 3];
-          const bf16x8 pb = __builtin_bit_cast(bf16x8, pu);
-#pragma unroll
-          for (int dt = 0; dt < C::DT; ++dt) {
-            const uint16_t* vp = reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(vr) + voff[dt] +
-                                                                   (32 * kt + 16 * half) * C::RB);
-            const s16x4 v0 = lds_read_tr(vp);
-            const s16x4 v1 = lds_read_tr(vp + 8 * D);
-            const s16x8 vv = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
-            acc_o[dt] =
-                __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv), pb, acc_o[dt], 0, 0, 0);
+      // The running max is only refreshed when the tile could break the bound
+      // p <= 2^8: a lane's sum of its P stays <= 2^8 whenever every p does, so a
+      // larger (or non-finite) sum in any lane sends the wave to the exact
+      // path -- the tile's max, a rescale of O (which holds the tiles up to
+      // t-1) and both sums to it, and the tile's P again (then p <= 1).
+      if (__builtin_amdgcn_ballot_w64(!(st <= 256.f))) {
+        const float mx = half_swap_max(tile_max(acc_s)) * sl2;
+        if (mx > m_run) {
+          // the max moves up by a whole number of binades (to >= mx), so the
+          // rescale of O and both sums is exact.  A jump past 2^128 (or the
+          // first key) drops the old terms, which are then below 2^-120 of
+          // the new ones.
+          float alpha = 0.f;
+          const float dm = mx - m_run;
+          if (dm > 128.f) {
+            m_run = mx;
+          } else {
+            const float k = ceilf(dm);
+            alpha = __builtin_amdgcn_ldexpf(1.f, -(int)k);
+            m_run += k;
           }
-          if constexpr (C::KT == 1) {
+          l_run *= alpha;
+          le_run *= alpha;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) le_run += pf[kt][8 * half + i];
-          }
+          for (int d = 0; d < C::DT; ++d)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc_o[d][e] *= alpha;
         }
-      if constexpr (C::DT == 4) {
-        // the first two MFMAs' V reads, then (P V MFMA + the V reads of the
-        // MFMA two ahead + VB VALU) for all but the last two MFMAs, then
-        // 2 x (MFMA + VB VALU); with one sub-tile per step the VALU work is the
-        // fp32 row sum, here where the VALU is idle rather than among the
-        // exponentials of phase A
-        constexpr int VB = C::KT == 1 ? 2 : 0;
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+        st = 0.f;
+        se = 0.f;
+        const float off = m_run == -INFINITY ? 0.f : -m_run;
 #pragma unroll
-        for (int i = 0; i < 8 * C::KT - 2; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-          if constexpr (VB > 0) __builtin_amdgcn_sched_group_barrier(0x002, VB, 0);
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          if constexpr (VB > 0) __builtin_amdgcn_sched_group_barrier(0x002, VB, 0);
+        for (int e = 0; e < NE; e += 2) {
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(acc_s[e / 16][e % 16], sl2, off));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(acc_s[e / 16][e % 16 + 1], sl2, off));
+          se += p0;
+          se += p1;
+          const uint32_t u = pack2_bf16(p0, p1);
+          st += __uint_as_float(u << 16) + __uint_as_float(u & 0xffff0000u);
+          pk[e / 16][e % 16 / 2] = u;
         }
       }
-      // keeps the fp32 row sum in this phase, among the P V MFMAs, rather than
-      // sunk into the next step ahead of its first score MFMA
-      if constexpr (C::KT == 1) asm volatile("" : "+v"(le_run));
-      if (t + 1 < ntiles && needs_mask(b1)) mask_tile(acc_n, b1);
-      __builtin_amdgcn_sched_barrier(0);
-      wait_vmcnt<3 * C::DPW>();  // K(t+2)
-      __syncthreads();
-      dma(vbase, b2, vr, vdma, 0u);
+      l_run += st;
+      le_run += se;
+      if (needs_mask(b1)) mask_tile(acc_n, b1);
 
 #pragma unroll
-      for (int kt = 0; kt < C::KT; ++kt) acc_s[kt] = acc_n[kt];
+      for (int kt = 0; kt < C::KT; ++kt) {
+        acc_s[kt] = acc_n[kt];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) pp[kt][i] = pk[kt][i];
+      }
       b1 = b2;
       b2 = b3;
       b3 = b4;
-      b4 = fetch(t + 5);
     };
-
     while (true) {
       step(std::integral_constant<int, 0>{});
       if (++t >= ntiles) break;
       step(std::integral_constant<int, 1>{});
       if (++t >= ntiles) break;
-      step(std::integral_constant<int, 2>{});
-      if (++t >= ntiles) break;
-      step(std::integral_constant<int, 3>{});
-      if (++t >= ntiles) break;
-      step(std::integral_constant<int, 4>{});
-      if (++t >= ntiles) break;
-      step(std::integral_constant<int, 5>{});
-      if (++t >= ntiles) break;
     }
+    // P V of the last tile, whose V the last step waited for
+#pragma unroll
+    for (int m = 0; m < VM; ++m) pv(m, read_v(vs[(ntiles - 1) % 2], m), pp);
     wait_vmcnt<0>();  // loads past the end of the list still write LDS
   }
 
@@ -666,7 +653,7 @@ void attn_fwd_kernel(AttnArgs a) {
   le_run = half_swap_sum(le_run);
   const int lane_o = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   const int l32o = lane_o % 32, hho = lane_o / 32;
-  const int64_t row_o = (int64_t)qb * BLK + qs * 32 + l32o;
+  const int64_t row_o = (int64_t)qg * (32 * NW) + wave * 32 + l32o;
   const bool row_ok = row_o < a.lq;
   if constexpr (SPLIT) {
     // Partial result of this key range: the unnormalised P V, scaled by a
@@ -684,7 +671,7 @@ void attn_fwd_kernel(AttnArgs a) {
     ex = ex < -126 ? -126 : ex;
     const float sc = __builtin_amdgcn_ldexpf(1.0f, -ex);
     if (row_ok) {
-      const int64_t prow = (work * a.n_splits + split) * BLK + qs * 32 + l32o;
+      const int64_t prow = ((bh * a.n_q + row_o / BLK) * a.n_splits + split) * BLK + row_o % BLK;
       _Float16* po = reinterpret_cast<_Float16*>(a.part_o) + prow * D;
 #pragma unroll
       for (int t = 0; t < C::DT; ++t)
@@ -820,30 +807,38 @@ __global__ __launch_bounds__((MergeCfg<D, BLK>::NT)) void attn_merge_kernel(Attn
 }
 
 template <int D, int BLK>
-static hipError_t launch_cfg(const AttnArgs& a, bool dense, hipStream_t stream) {
+static hipError_t launch_merge(const AttnArgs& a, hipStream_t stream) {
   const int64_t items = (int64_t)a.bh * a.n_q;
-  if (items == 0) return hipSuccess;
-  constexpr int NT = AttnCfg<D, BLK>::NT;
-  if (a.part_o != nullptr) {
-    if (a.n_splits != 8 && a.n_splits != kSplits) return hipErrorInvalidValue;
-    if (dense) attn_fwd_kernel<D, BLK, true, true><<<items * a.n_splits, NT, 0, stream>>>(a);
-    else attn_fwd_kernel<D, BLK, false, true><<<items * a.n_splits, NT, 0, stream>>>(a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (a.n_splits == 8) attn_merge_kernel<D, BLK, 8><<<items, MergeCfg<D, BLK>::NT, 0, stream>>>(a);
-    else attn_merge_kernel<D, BLK, kSplits><<<items, MergeCfg<D, BLK>::NT, 0, stream>>>(a);
-  } else {
-    if (dense) attn_fwd_kernel<D, BLK, true, false><<<items, NT, 0, stream>>>(a);
-    else attn_fwd_kernel<D, BLK, false, false><<<items, NT, 0, stream>>>(a);
-  }
+  constexpr int NT = MergeCfg<D, BLK>::NT;
+  if (a.n_splits == 8) attn_merge_kernel<D, BLK, 8><<<items, NT, 0, stream>>>(a);
+  else if (a.n_splits == kSplits) attn_merge_kernel<D, BLK, kSplits><<<items, NT, 0, stream>>>(a);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
+template <int D, int BLK, int NW, bool DENSE>
+static hipError_t launch_cfg(const AttnArgs& a, hipStream_t stream) {
+  const int64_t groups = (int64_t)a.bh * ((a.lq + 32 * NW - 1) / (32 * NW));
+  if (groups == 0) return hipSuccess;
+  if (a.part_o == nullptr) {
+    attn_fwd_kernel<D, BLK, NW, DENSE, false><<<groups, 64 * NW, 0, stream>>>(a);
+    return hipGetLastError();
+  }
+  attn_fwd_kernel<D, BLK, NW, DENSE, true><<<groups * a.n_splits, 64 * NW, 0, stream>>>(a);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  return launch_merge<D, BLK>(a, stream);
+}
+
+template <int D, int BLK>
+static hipError_t launch_mode(const AttnArgs& a, bool dense, hipStream_t stream) {
+  return dense ? launch_cfg<D, BLK, 4, true>(a, stream) : launch_cfg<D, BLK, BLK / 32, false>(a, stream);
+}
+
 hipError_t launch_attn(const AttnArgs& a, int d, int block, bool dense, hipStream_t stream) {
-  if (d == 128 && block == 64) return launch_cfg<128, 64>(a, dense, stream);
-  if (d == 128 && block == 128) return launch_cfg<128, 128>(a, dense, stream);
-  if (d == 64 && block == 64) return launch_cfg<64, 64>(a, dense, stream);
-  if (d == 64 && block == 128) return launch_cfg<64, 128>(a, dense, stream);
+  if (d == 128 && block == 64) return launch_mode<128, 64>(a, dense, stream);
+  if (d == 128 && block == 128) return launch_mode<128, 128>(a, dense, stream);
+  if (d == 64 && block == 64) return launch_mode<64, 64>(a, dense, stream);
+  if (d == 64 && block == 128) return launch_mode<64, 128>(a, dense, stream);
   return hipErrorInvalidValue;
 }
 
