@@ -11,7 +11,22 @@
 //
 // Order of the work (XCDs and L2).  Work-groups go round-robin over the eight
 // XCDs.  The id decodes so that each XCD runs the query groups of one (head, key
-// range) pair after the other, and its L2 holds one range of the head's K/V.
+// range) pair after the other.  The work-groups in flight on an XCD (8,192 rows
+// at D = 128) then read the same range of K/V, but those that started earlier
+// are further along their lists, so between them they touch all of the range.
+// With several ranges, the i-th work-group of a pair therefore starts its list
+// at the fraction (i mod C) / C of the range and wraps around, C being the
+// number of work-groups in flight: when it starts, the one k before it has done
+// about k / C of its list and has just reached the same place, and those in
+// flight share a narrow moving window of K/V.  Ranges need not fit the 4 MB L2
+// any more, and fewer of them write fewer partial results: at 24 heads, 72,000
+// queries, 144,512 keys and 25% density the call took 33.2 ms rotated and 52.8
+// plain with 4 ranges (8 ranges: 32.8 and 38.1; 16: 34.5 and 36.0; 2: 36.6 and
+// 64.4).  Work-groups that run in step by themselves keep the plain order: the
+// dense call and lists that can name every block (27.8 ms plain, 29.9 rotated,
+// at 25,920 queries and 98,432 keys), the first rounds of a call, and one
+// range over the whole sequence, which the window loses (mid scale 5.3 rotated
+// and 4.7 plain).
 //
 // Per tile of the query block's key-block list, a three-stage pipeline: step t
 // runs the scores of tile t + 1, the softmax of tile t and P V of tile t - 1.
@@ -47,12 +62,12 @@
 // O = O^T / l in bf16 with l the row sum of the bf16-rounded P, and
 // lse = ln2*(m + log2 le) with le the row sum of the unrounded fp32 p.
 //
-// What bounds it (24 heads, D = 128, one box): the dense call runs at 1.17
-// PFLOP/s against 1.28 for a large library GEMM; the matrix cores are busy 63%
-// of the cycles at 1.65 GHz, the clock the chip holds under this load.  The sparse
-// call at b = 64 streams 64 KB of K/V per 64 x 128 tile pair from L2, as many
-// texture-path clocks as MFMA clocks, and without those loads would take 25.6
-// instead of 33.4 ms.
+// What bounds it (24 heads, D = 128): the dense call runs at 1.10 to 1.16
+// PFLOP/s against 1.28 for a large library GEMM on the same card; the matrix
+// cores are busy 63% of the cycles at 1.65 GHz, the clock the chip holds under
+// this load, and power sets that clock.  The sparse call at b = 64 moves 32 KB of
+// K/V per 64 x 64 tile from L2 to LDS, as many texture-path clocks as MFMA
+// clocks; without those loads it would take 25.6 instead of 33.4 ms.
 //
 // MFMA layouts (v_mfma_f32_32x32x16_bf16, lane l, h = l / 32):
 //   A[m][k]: m = l % 32, k = 8h + i (i = 0..7 of the lane's bf16x8)
@@ -214,26 +229,23 @@ void attn_fwd_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) uint16_t vs[C::NV][C::TILE];
 
   // Work item: query group qg of the (head, range) pair bh * n_splits + split.
-  // Eight pairs at a time run side by side, pair 8 i + x on XCD x; the query
-  // groups of the last (fewer than eight) pairs are dealt out to the XCDs in
-  // eight equal consecutive shares.
-  const int n_g = DENSE ? (int)((a.lq + 32 * NW - 1) / (32 * NW)) : a.n_q;  // query groups per head
-  const int n_ranges = SPLIT ? a.n_splits : 1;
-  const int64_t pairs = (int64_t)a.bh * n_ranges, whole = pairs / 8 * 8;
-  int64_t pair, id = blockIdx.x;
-  int qg;
-  if (id < whole * n_g) {
-    pair = id / 8 / n_g * 8 + id % 8;
-    qg = (int)(id / 8 % n_g);
-  } else {
-    id = xcd_linear(id - whole * n_g, (pairs - whole) * n_g);
-    pair = whole + id / n_g;
-    qg = (int)(id % n_g);
-  }
-  const int64_t bh = pair / n_ranges;
-  const int split = (int)(pair % n_ranges);
-  const int blk_lo = (int)((int64_t)split * a.n_k / n_ranges);
-  const int blk_hi = (int)((int64_t)(split + 1) * a.n_k / n_ranges);
+  // A pair's groups are dealt out to 2^spread_bits XCDs (a unit: the pair's groups
+  // on one of them).  Units go to the XCDs eight at a time, turned by one XCD
+  // each time, so that every XCD gets every range in turn: forced blocks make
+  // some ranges several times as long as others (reference and text forced at
+  // 720p: 79 ms turned, 122 unturned).  An XCD runs a unit's groups one after the
+  // other.  (All of it fits 32 bits, as the grid does.)
+  const uint32_t n_g = DENSE ? (uint32_t)((a.lq + 32 * NW - 1) / (32 * NW)) : (uint32_t)a.n_q;  // groups per head
+  const uint32_t range_bits = SPLIT ? __builtin_ctz(a.n_splits) : 0;  // n_splits is a power of two
+  const uint32_t n_u = (n_g + (1u << a.spread_bits) - 1) >> a.spread_bits;
+  const uint32_t id = blockIdx.x / 8, ui = id / n_u, gi = id - ui * n_u;
+  const uint32_t unit = ui * 8 + (blockIdx.x + ui) % 8, pair = unit >> a.spread_bits;
+  const int qg = (int)((gi << a.spread_bits) + (unit & ((1u << a.spread_bits) - 1)));
+  if (pair >= ((uint32_t)a.bh << range_bits) || qg >= (int)n_g) return;  // uniform: past the last unit or group
+  const int64_t bh = pair >> range_bits;
+  const int split = (int)(pair & ((1u << range_bits) - 1));
+  const int blk_lo = (int)(((int64_t)split * a.n_k) >> range_bits);
+  const int blk_hi = (int)(((int64_t)(split + 1) * a.n_k) >> range_bits);
 
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -252,42 +264,59 @@ void attn_fwd_kernel(AttnArgs a) {
 
   // ---- the list positions [pos_lo, pos_lo + cnt) that hold the blocks of
   // [blk_lo, blk_hi): an ascending list has them after the entries < blk_lo and
-  // before the entries >= blk_hi (every wave counts them itself)
-  int pos_lo, cnt;
+  // before the entries >= blk_hi (every wave counts them itself).  The walk
+  // starts at position pos_lo + rot, the first entry >= blk_st, and wraps.
+  int pos_lo, cnt, rot = 0;
   const int32_t* list = nullptr;
   if constexpr (DENSE) {
     pos_lo = blk_lo;
     cnt = blk_hi - blk_lo;
   } else {
+    int blk_st = blk_lo;
+    if (a.rotation > 0) {
+      const uint32_t phase = gi % (uint32_t)a.rotation;
+      blk_st += (int)((int64_t)phase * (blk_hi - blk_lo) / a.rotation);
+    }
     const int64_t r = bh * a.n_q + qg;
     int nblk = a.kv_num_blocks[r];
     nblk = nblk < 0 ? 0 : (nblk > a.stride ? a.stride : nblk);
     list = a.kv_indices + r * a.stride;
-    // 64 x U entries per pass, all loads independent (one memory latency per
-    // pass); the counts come from ballots, so they are wave-uniform at once
-    constexpr int U = 12;
-    int c_lo = 0, c_hi = 0;
-    // (the first pass does not wait for the count: it reads up to the stride)
-    for (int base = 0; base == 0 || base < nblk; base += 64 * U) {
-      int v[U];
+    if (!SPLIT && a.rotation == 0) {
+      // the whole list from its head: nothing to look for
+      pos_lo = 0;
+      cnt = __builtin_amdgcn_readfirstlane(nblk);
+    } else {
+      // 64 x U entries per pass, all loads independent (one memory latency per
+      // pass); the counts come from ballots, so they are wave-uniform at once
+      constexpr int U = 12;
+      int c_lo = 0, c_hi = 0, c_st = 0;
+      // (the first pass does not wait for the count: it reads up to the stride)
+      for (int base = 0; base == 0 || base < nblk; base += 64 * U) {
+        int v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = base + 64 * u + lane;
-        v[u] = i < a.stride ? list[i] : 0x7fffffff;
-      }
+        for (int u = 0; u < U; ++u) {
+          const int i = base + 64 * u + lane;
+          v[u] = i < a.stride ? list[i] : 0x7fffffff;
+        }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bool in = base + 64 * u + lane < nblk;
-        c_lo += __builtin_popcountll(__builtin_amdgcn_ballot_w64(in && v[u] < blk_lo));
-        c_hi += __builtin_popcountll(__builtin_amdgcn_ballot_w64(in && v[u] < blk_hi));
+        for (int u = 0; u < U; ++u) {
+          const bool in = base + 64 * u + lane < nblk;
+          c_lo += __builtin_popcountll(__builtin_amdgcn_ballot_w64(in && v[u] < blk_lo));
+          c_hi += __builtin_popcountll(__builtin_amdgcn_ballot_w64(in && v[u] < blk_hi));
+          c_st += __builtin_popcountll(__builtin_amdgcn_ballot_w64(in && v[u] < blk_st));
+        }
       }
+      pos_lo = __builtin_amdgcn_readfirstlane(c_lo);
+      cnt = __builtin_amdgcn_readfirstlane(c_hi) - pos_lo;
+      rot = __builtin_amdgcn_readfirstlane(c_st) - pos_lo;
+      // (out of [0, cnt) only past the range's last entry, or in a list that is
+      // not ascending)
+      if (rot < 0 || rot >= cnt) rot = 0;
     }
-    pos_lo = __builtin_amdgcn_readfirstlane(c_lo);
-    cnt = __builtin_amdgcn_readfirstlane(c_hi) - pos_lo;
   }
 
   // ---- the key tiles of the item.  Tile j (KB keys) is tile j % SUB of the key
-  // block at list position pos_lo + j / SUB.  The entries are held 64 at a time
+  // block at the walk's entry j / SUB.  The entries are held 64 at a time
   // in a VGPR (lane i: entry lbase + i, as its first tile) and picked out with
   // v_readlane, so the loop issues no memory load of its own except one batch
   // load per 64 entries.  j >= cnt * SUB, and an entry outside [blk_lo, blk_hi)
@@ -297,7 +326,8 @@ void attn_fwd_kernel(AttnArgs a) {
   auto load_batch = [&](int base) {
     lbase = base;
     if constexpr (!DENSE) {
-      const int b = base + lane < cnt ? list[pos_lo + base + lane] : -1;
+      const int e = base + lane + rot;
+      const int b = base + lane < cnt ? list[pos_lo + (e >= cnt ? e - cnt : e)] : -1;
       lreg = (b >= blk_lo && b < blk_hi) ? b * C::SUB : -C::SUB;
       // consume the load here, so that its wait stays on this rare path and is
       // not merged into the common path of the loop
@@ -810,28 +840,52 @@ template <int D, int BLK>
 static hipError_t launch_merge(const AttnArgs& a, hipStream_t stream) {
   const int64_t items = (int64_t)a.bh * a.n_q;
   constexpr int NT = MergeCfg<D, BLK>::NT;
-  if (a.n_splits == 8) attn_merge_kernel<D, BLK, 8><<<items, NT, 0, stream>>>(a);
-  else if (a.n_splits == kSplits) attn_merge_kernel<D, BLK, kSplits><<<items, NT, 0, stream>>>(a);
+  if (a.n_splits == 2) attn_merge_kernel<D, BLK, 2><<<items, NT, 0, stream>>>(a);
+  else if (a.n_splits == 4) attn_merge_kernel<D, BLK, 4><<<items, NT, 0, stream>>>(a);
+  else if (a.n_splits == 8) attn_merge_kernel<D, BLK, 8><<<items, NT, 0, stream>>>(a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 template <int D, int BLK, int NW, bool DENSE>
-static hipError_t launch_cfg(const AttnArgs& a, hipStream_t stream) {
-  const int64_t groups = (int64_t)a.bh * ((a.lq + 32 * NW - 1) / (32 * NW));
-  if (groups == 0) return hipSuccess;
+static hipError_t launch_cfg(const AttnArgs& args, hipStream_t stream) {
+  const int64_t n_g = (args.lq + 32 * NW - 1) / (32 * NW);  // query groups per head
+  if (n_g == 0) return hipSuccess;
+  AttnArgs a = args;
+  // How many XCDs share a (head, range) pair.  One keeps the pair's K/V in one
+  // L2, but an XCD with only a few pairs runs as long as its heads' lists are
+  // (per-head budgets differ).  So a pair is shared until each XCD has four
+  // units, as long as a unit keeps 4,096 query rows (half of what an XCD holds):
+  // 8 heads with budgets from 0.5 to 1.5 of the mean, 21,332 queries, took
+  // 0.56 ms shared by four and 0.71 unshared; 6,413 queries 0.62 and 0.44.  The
+  // units of all pairs have to deal out evenly in any case.
+  const int64_t pairs = (int64_t)a.bh * a.n_splits;
+  auto enough = [&](int bits) {
+    const int64_t units = pairs << bits;
+    return units % 8 == 0 && (units >= 32 || ((n_g * 32 * NW) >> (bits + 1)) < 4096);
+  };
+  a.spread_bits = 0;
+  while (a.spread_bits < 3 && !enough(a.spread_bits)) ++a.spread_bits;
+  const int64_t units = ((pairs << a.spread_bits) + 7) / 8 * 8;
+  const int64_t grid = units * ((n_g + (1 << a.spread_bits) - 1) >> a.spread_bits);
   if (a.part_o == nullptr) {
-    attn_fwd_kernel<D, BLK, NW, DENSE, false><<<groups, 64 * NW, 0, stream>>>(a);
+    attn_fwd_kernel<D, BLK, NW, DENSE, false><<<grid, 64 * NW, 0, stream>>>(a);
     return hipGetLastError();
   }
-  attn_fwd_kernel<D, BLK, NW, DENSE, true><<<groups * a.n_splits, 64 * NW, 0, stream>>>(a);
+  attn_fwd_kernel<D, BLK, NW, DENSE, true><<<grid, 64 * NW, 0, stream>>>(a);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   return launch_merge<D, BLK>(a, stream);
 }
 
 template <int D, int BLK>
 static hipError_t launch_mode(const AttnArgs& a, bool dense, hipStream_t stream) {
-  return dense ? launch_cfg<D, BLK, 4, true>(a, stream) : launch_cfg<D, BLK, BLK / 32, false>(a, stream);
+  if (!dense) return launch_cfg<D, BLK, BLK / 32, false>(a, stream);
+  // 128-row groups, but 64 rows where those would be so few that most CUs stay
+  // idle (1,056 queries of one head: 13.8 us against 15.9), or would pad a
+  // short query sequence by more than a tenth (774 queries of 10 heads: 154 and 158)
+  const int64_t wide = (a.lq + 127) / 128, narrow = (a.lq + 63) / 64, n_wide = wide * a.bh * a.n_splits;
+  if (n_wide <= 64 || (n_wide > 256 && 20 * wide > 11 * narrow)) return launch_cfg<D, BLK, 2, true>(a, stream);
+  return launch_cfg<D, BLK, 4, true>(a, stream);
 }
 
 hipError_t launch_attn(const AttnArgs& a, int d, int block, bool dense, hipStream_t stream) {

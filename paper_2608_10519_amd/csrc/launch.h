@@ -101,18 +101,14 @@ struct AttnArgs {
   uint16_t* part_o;   // [BH * n_q, n_splits, BLK, D] fp16: the range's unnormalised P V times 2^-e per row
   float* part_meta;   // [BH * n_q, n_splits, BLK, 4]: running max (log2 units), row sum of the bf16 P,
                       // row sum of the fp32 p, e (the row's power-of-two scale, as a float)
-  int n_splits;       // key ranges per query block: 8 or kSplits
+  int n_splits;       // key ranges per query block: 2, 4 or 8 with part_o, else 1
+  int rotation;       // work-groups in flight per XCD, for the start of each list; 0: start at its head
+  int spread_bits;    // log2 of the XCDs that share a (head, range) pair (set by the launcher)
 };
 
-// Key ranges per query block: each XCD takes n_splits / 8 of them (x, x + 8, ...)
-// one after the other, so that its 4 MB L2 holds about one range of a head's
-// K/V at a time.  kSplits
-// is the most (and the workspace is sized for it); short lists take 8 ranges,
-// where the per-range fixed cost (list scan, Q load, epilogue, partial result
-// and its merge) outweighs the L2 locality of the narrower ranges.
+// The split workspace holds this many key ranges per query block (attn_plan
+// takes at most 8 of them), and sequences of fewer key blocks are never split.
 constexpr int kSplits = 16;
-// Lists that can hold fewer keys than this (kv_stride x block size) take 8 ranges.
-constexpr int64_t kFewRangesBelowKeys = 24576;
 
 // Bytes of the fp16 partial-O region of the split workspace (256-byte aligned;
 // the per-row records follow it).

@@ -764,3 +764,62 @@ def test_attention_writes_only_its_outputs(gpu_lib, dense, split):
                                lists_h[h], w.block) for h in range(w.heads)]
     check_output(bf16_tensor_to_f64(o), np.stack([r[0] for r in refs])[None], lse.cpu().numpy().astype(np.float64),
                  np.stack([r[1] for r in refs])[None], what="guarded")
+
+
+# The cuts of the attention plan: (name, heads, Lq, Lk, D, b, listed blocks).
+# By the plan's estimate they take 1, 2, 4 and 8 key ranges; the next two are one
+# range in several rounds of items, with units of one XCD and shared ones; the
+# last three take several ranges and enough rounds (65,536 rows each at D = 128,
+# 98,304 at D = 64) that the lists are walked from a rotated start.
+PLAN_CASES = [
+    ("one-range", 3, 64 * 5 + 1, 64 * 20 + 3, 128, 64, 4),
+    ("two-ranges", 24, 64 * 16, 64 * 172 + 5, 128, 64, 53),
+    ("four-ranges", 2, 64 * 9 + 7, 64 * 40 + 9, 128, 64, 20),
+    ("eight-ranges", 1, 128 * 16 + 1, 128 * 64 + 77, 64, 128, 38),
+    ("many-rounds", 64, 64 * 128, 64 * 160 + 11, 128, 64, 90),
+    ("shared-units", 3, 64 * 300 + 5, 64 * 310, 64, 64, 17),
+    ("rotated-d64", 32, 64 * 150, 64 * 2700 + 1, 64, 64, 300),
+    ("rotated-b128", 24, 128 * 60 - 3, 128 * 700, 128, 128, 100),
+    ("rotated-four-ranges", 24, 64 * 120 - 1, 64 * 1300 + 13, 128, 64, 330),
+]
+
+
+@pytest.mark.parametrize("name,heads,lq,lk,d,b,n", PLAN_CASES, ids=[c[0] for c in PLAN_CASES])
+def test_plan_cuts_match_oracle(gpu_lib, name, heads, lq, lk, d, b, n):
+    """Every cut of the attention call (key ranges, rotated lists) on random
+    lists, some of them shorter (one empty), with the partial last block in half
+    of them: sampled query blocks against the oracle; the single pass and, with
+    the same lists in a kv_stride that could hold every block (never rotated,
+    planned as a full list), the plain walk, against the same bounds."""
+    import torch
+
+    _say(f"[plan] {name}: H={heads} Lq={lq} Lk={lk} D={d} b={b} n={n}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(71)
+    n_q, n_k = -(-lq // b), -(-lk // b)
+    q, k, v = (torch.randn(1, heads, l, d, generator=g, device="cuda").to(torch.bfloat16) for l in (lq, lk, lk))
+    r = torch.rand(1, heads, n_q, n_k, generator=g, device="cuda")
+    r[:, :, ::2, -1] = -1.0  # the partial last key block
+    idx = r.topk(n, dim=-1, largest=False).indices.sort(dim=-1).values.to(torch.int32)
+    num = torch.full((1, heads, n_q), n, dtype=torch.int32, device="cuda")
+    num[:, :, 1] = n // 2
+    num[0, heads - 1, 2] = 0
+    wide = torch.zeros(1, heads, n_q, n_k, dtype=torch.int32, device="cuda")
+    wide[..., :n] = idx
+    runs = {"plan": gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, b),
+            "one pass": gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, b, split=False),
+            "plain": gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, wide, b)}
+    again = gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, b)
+    torch.cuda.synchronize()
+    assert torch.equal(again[0], runs["plan"][0]) and torch.equal(again[1], runs["plan"][1])
+    nums, lists = num.cpu().numpy(), idx.cpu().numpy()
+    for h in sorted({0, heads // 2, heads - 1}):
+        kh, vh = bf16_tensor_to_f64(k[0, h]), bf16_tensor_to_f64(v[0, h])
+        for i in sorted({0, 1, 2, n_q // 2, n_q - 1}):
+            t = slice(i * b, min((i + 1) * b, lq))
+            o_ref, l_ref = O.sparse_attention(bf16_tensor_to_f64(q[0, h, t]), kh, vh,
+                                              [lists[0, h, i, : nums[0, h, i]].tolist()], b)
+            for what, (o, lse) in runs.items():
+                check_output(bf16_tensor_to_f64(o[0, h, t])[None], o_ref[None],
+                             lse[0, h, t].cpu().numpy().astype(np.float64)[None], l_ref[None],
+                             what=f"{name} {what} head {h} block {i}")
