@@ -167,6 +167,29 @@ def test_token_topk_mass_d128_ragged(gpu_lib, sharp):
     _topk_case(gpu_lib, q, k, rows, n_tok, scale)
 
 
+@pytest.mark.parametrize("lk,d,n_rows,distinct", [(32_768, 64, 16, 0), (32_769, 128, 3, 0), (40_001, 128, 16, 0),
+                                                  (70_003, 64, 1, 0), (40_004, 64, 4, 7), (33_000, 128, 2, 1)])
+def test_token_topk_mass_long_rows(gpu_lib, lk, d, n_rows, distinct):
+    """Rows at and past the 32,768 keys that are searched whole, where the n-th
+    largest is bracketed from 512 samples: counts at both ends, around the
+    bracket's edge ranks and in the middle, key counts that are no multiple of 4,
+    and keys repeated so often (7 distinct ones, 1) that the bracket overflows
+    and the row is searched from memory."""
+    _say(f"[mass] token top-n long rows Lk={lk} D={d} rows={n_rows} distinct={distinct}")
+    rng = np.random.default_rng(lk + d)
+    H, Lq = 2, 20
+    from synthetic.workloads import bf16_bits
+
+    q = bf16_bits(rng.standard_normal((1, H, Lq, d)).astype(np.float32))
+    k = rng.standard_normal((1, H, distinct or lk, d)).astype(np.float32)
+    if distinct:
+        k = k[:, :, np.arange(lk) % distinct]
+    rows = list(range(Lq - n_rows, Lq))
+    picks = [1, 2, 20, lk // 256, lk // 100, lk // 10, lk // 4, lk // 2, lk - lk // 50, lk - 3, lk - 1, lk, 0, lk + 9]
+    n_tok = [[picks[(7 * h + r) % len(picks)] for r in range(n_rows)] for h in range(H)]
+    _topk_case(gpu_lib, q, bf16_bits(k), rows, n_tok)
+
+
 def test_mass_at_720p_sampled(gpu_lib):
     """The 720p final scale (72,000 queries, 144,512 keys, D = 128, b = 64,
     rho = 0.25), two heads: the block selection's retained mass from the two
