@@ -119,11 +119,13 @@ __global__ __launch_bounds__(64 * kSelWaves) void select_kernel(SelectArgs a) {
   if (lane == 0) a.kv_num_blocks[r] = pos;
 }
 
-// Forced blocks and blocks past n_k hold key 0, below every real key (the
-// smallest order key of a non-NaN float is 0x007fffff), so they never count.
+// Forced blocks hold key 0 and blocks past n_k key 1, below every real key (the
+// smallest order key of a non-NaN float is 0x007fffff), so they never count: no
+// helper counts from below kLeastKey.
 //
 // The keys of a row sit in registers: key[c] of lane L is the key of block
 // 64 c + L.  Every helper below is called by every lane of the wave.
+constexpr uint32_t kForcedKey = 0u, kPastKey = 1u, kLeastKey = 2u;
 
 // Number of keys >= x (wave-uniform).
 template <int C>
@@ -231,15 +233,15 @@ __device__ __forceinline__ void sort_samples_desc(uint32_t (&s)[2], int lane) {
 // samp[1]: sample 64 + L; 0 for forced ones).  The sampled keys of the ranks
 // around the expected rank of the kk-th key (a margin of about 2.2 standard
 // deviations of the binomial count), read off the sorted sample, give
-// thresholds t_lo <= t_hi; two counts over the row
-// check that the kk-th key lies in [t_lo, t_hi), and the keys there (a few
-// hundred) are compacted through the wave's LDS buffer `buf` (64 kSelCand
-// words) and searched alone.  When the bracket misses or holds too many keys,
-// the whole row is searched.
-template <int C>
+// thresholds t_lo <= t_hi.  The keys in [t_lo, t_hi) (a few hundred) are
+// compacted through the wave's LDS buffer `buf`, counted on the way, and searched
+// alone.  buf holds up to 64 kSelCand of them; with DUMP it has one more word,
+// which takes the lanes with nothing to store, so that the loop has no branch.
+// When the bracket misses or holds too many keys, the whole row is searched.
+template <int C, bool DUMP>
 __device__ __forceinline__ SelRule rule_sampled(const uint32_t (&key)[C], int kk, int n_sel, const uint32_t (&samp)[2],
                                                 uint32_t* buf, int lane) {
-  const int s_real = count_ge<2>(samp, 1u);
+  const int s_real = count_ge<2>(samp, kLeastKey);
   if (s_real >= 16 && n_sel > 0 && kk < n_sel) {
     const float p = (float)kk / (float)n_sel;
     const float mid = p * (float)s_real;  // expected number of sampled keys >= the kk-th key
@@ -255,19 +257,23 @@ __device__ __forceinline__ SelRule rule_sampled(const uint32_t (&key)[C], int kk
                     : (uint32_t)__builtin_amdgcn_readlane((int)ss[1], e - 64);
     };
     const uint32_t t_hi = has_hi ? kth(r1) : 0u;
-    const uint32_t t_lo = r2 <= s_real ? kth(r2) : 1u;
+    const uint32_t t_lo = r2 <= s_real ? kth(r2) : kLeastKey;
     const int g_hi = has_hi ? count_ge<C>(key, t_hi) : 0;  // keys above the range
-    const int g_lo = count_ge<C>(key, t_lo);
-    const int m = g_lo - g_hi;                             // keys in [t_lo, t_hi)
-    if (g_hi < kk && kk <= g_lo && m <= 64 * kSelCand) {
-      int base = 0;
+    if (g_hi < kk) {
+      // key in [t_lo, t_hi) as one unsigned compare (t_hi = 0: no upper end)
+      const uint32_t span = t_hi - t_lo;
+      constexpr int kDump = 64 * kSelCand;
+      int m = 0;  // keys in the range
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const bool in = key[c] >= t_lo && (!has_hi || key[c] < t_hi);
+        const bool in = key[c] - t_lo < span;
         const uint64_t mask = __ballot(in);
-        if (in) buf[base + lanes_below(mask)] = key[c];
-        base += __popcll(mask);
+        const int pos = m + lanes_below(mask);
+        if constexpr (DUMP) buf[in && pos < kDump ? pos : kDump] = key[c];
+        else if (in && pos < kDump) buf[pos] = key[c];
+        m += __popcll(mask);
       }
+      if (kk > g_hi + m || m > kDump) return rule_full<C>(key, kk);
       const uint32_t upper = has_hi ? t_hi - 1 : 0xffffffffu;
       if (m <= 64 * 4) return rule_from_candidates<4>(buf, m, lane, kk, g_hi, t_lo, upper);
       if (m <= 64 * 8) return rule_from_candidates<8>(buf, m, lane, kk, g_hi, t_lo, upper);
@@ -277,37 +283,34 @@ __device__ __forceinline__ SelRule rule_sampled(const uint32_t (&key)[C], int kk
   return rule_full<C>(key, kk);
 }
 
-// Writes the row's list: the forced blocks and the selected ones, ascending.
-// A block is forced when it lies below n_k and holds key 0 (real keys are
-// >= 0x007fffff).  Without ties to break (take_ties == 0, the usual case) a
-// block is taken when forced or above thr.
+// Writes the row's list of at most `stride` entries: the forced blocks and the
+// selected ones, ascending.  Without ties to break (take_ties == 0, the usual
+// case) a block is taken when forced or above thr: key - 1 >= thr as unsigned,
+// which holds for the forced key 0 and not for a block past n_k (thr is at least
+// the least real key less one).  The stores go through a buffer descriptor, the
+// lanes that take nothing past its end, so that the loop has no branch.
 template <int C>
-__device__ __forceinline__ void emit_row(const uint32_t (&key)[C], int n_k, SelRule rule, int lane, int32_t* out,
+__device__ __forceinline__ void emit_row(const uint32_t (&key)[C], SelRule rule, int lane, int32_t* out, int cap,
                                          int32_t* num_out) {
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(out, (short)0, cap * 4, 0x00020000);
   int pos = 0;
+  auto put = [&](bool take, int c) {
+    const uint64_t mask = __ballot(take);
+    const int at = pos + lanes_below(mask);
+    __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(64 * c + lane), rs, take ? at * 4 : -4, 0, 0);
+    pos += __popcll(mask);
+  };
   if (rule.take_ties == 0) {
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      if (64 * c >= n_k) break;
-      const bool valid = 64 * c + 64 <= n_k || 64 * c + lane < n_k;
-      const bool take = key[c] > rule.thr || (key[c] == 0u && valid);
-      const uint64_t take_mask = __ballot(take);
-      if (take) out[pos + lanes_below(take_mask)] = 64 * c + lane;
-      pos += __popcll(take_mask);
-    }
+    for (int c = 0; c < C; ++c) put(key[c] - 1u >= rule.thr, c);
   } else {
     uint32_t ties = 0;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      if (64 * c >= n_k) break;
-      const bool valid = 64 * c + 64 <= n_k || 64 * c + lane < n_k;
-      const bool tie = key[c] == rule.thr;  // thr >= 1: never a forced block
+      const bool tie = key[c] == rule.thr;  // thr >= kLeastKey: never a forced block
       const uint64_t tie_mask = __ballot(tie);
       const uint32_t tie_rank = ties + (uint32_t)lanes_below(tie_mask);
-      const bool take = key[c] > rule.thr || (tie && tie_rank < rule.take_ties) || (key[c] == 0u && valid);
-      const uint64_t take_mask = __ballot(take);
-      if (take) out[pos + lanes_below(take_mask)] = 64 * c + lane;
-      pos += __popcll(take_mask);
+      put(key[c] - 1u >= rule.thr || (tie && tie_rank < rule.take_ties), c);
       ties += (uint32_t)__popcll(tie_mask);
     }
   }
@@ -337,10 +340,13 @@ __device__ __forceinline__ int sample_block(int i, int n_k) { return (int)(((2 *
 
 // Rows of up to 64 C blocks: one wave per row reads its row of S straight
 // into registers (coalesced, 256 bytes per load) through one buffer
-// descriptor, so that loads past n_k need no clamp (they read 0).
-template <int C>
+// descriptor, so that loads past n_k need no clamp (they read 0).  Bound by the
+// instructions of a row (some 35 a chunk of 64 keys at C = 36), not by S: 27,000
+// rows of 2,259 blocks take 97 us, 102 with a second count of the bracket and
+// branches around each store; 244 MB of S at the copy rate are 50.
+template <int C, bool SAMPLED>
 __global__ __launch_bounds__(64 * kSelWaves) void select_reg_kernel(SelectArgs a) {
-  __shared__ uint32_t cbuf[kSelWaves][64 * kSelCand];
+  __shared__ uint32_t cbuf[kSelWaves][SAMPLED ? 64 * kSelCand + 4 : 1];
   // the wave index as a scalar, so that the row's descriptor is one too
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int64_t row = (int64_t)blockIdx.x * kSelWaves + wave;
@@ -353,21 +359,31 @@ __global__ __launch_bounds__(64 * kSelWaves) void select_reg_kernel(SelectArgs a
   uint32_t key[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(rs, (64 * c + lane) * 4, 0, 2);
+  uint32_t sp[2] = {0u, 0u};
   const int b0 = sample_block(lane, a.n_k), b1 = sample_block(64 + lane, a.n_k);
-  const uint32_t sp0 = __builtin_amdgcn_raw_buffer_load_b32(rs, b0 * 4, 0, 0);
-  const uint32_t sp1 = __builtin_amdgcn_raw_buffer_load_b32(rs, b1 * 4, 0, 0);
+  if constexpr (SAMPLED) {
+    sp[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, b0 * 4, 0, 0);
+    sp[1] = __builtin_amdgcn_raw_buffer_load_b32(rs, b1 * 4, 0, 0);
+  }
   const uint64_t fm = forced_mask(a.keep, lane);
 #pragma unroll
   for (int c = 0; c < C; ++c) {
-    const bool real = (64 * c + 64 <= a.n_k || 64 * c + lane < a.n_k) && !((fm >> c) & 1ull);
-    key[c] = real ? order_key_bits(key[c]) : 0u;
+    key[c] = (fm >> c) & 1ull ? kForcedKey : order_key_bits(key[c]);
+    key[c] = 64 * c + lane < a.n_k ? key[c] : kPastKey;
   }
-  const uint32_t samp[2] = {keep_block(a.keep, b0) ? 0u : order_key_bits(sp0),
-                            keep_block(a.keep, b1) ? 0u : order_key_bits(sp1)};
   const int kk = a.budget.k[h];
-  // kk == 0: nothing selectable
-  const SelRule rule = kk > 0 ? rule_sampled<C>(key, kk, a.n_sel, samp, cbuf[wave], lane) : SelRule{0xffffffffu, 0u};
-  emit_row<C>(key, a.n_k, rule, lane, a.kv_indices + row * a.stride, a.kv_num_blocks + row);
+  SelRule rule{0xffffffffu, 0u};  // kk == 0: nothing selectable
+  if (kk > 0) {
+    if constexpr (SAMPLED) {
+      const uint32_t samp[2] = {keep_block(a.keep, b0) ? 0u : order_key_bits(sp[0]),
+                                keep_block(a.keep, b1) ? 0u : order_key_bits(sp[1])};
+      rule = rule_sampled<C, true>(key, kk, a.n_sel, samp, cbuf[wave], lane);
+    } else {
+      rule = rule_full<C>(key, kk);
+    }
+  }
+  emit_row<C>(key, rule, lane, a.kv_indices + row * a.stride, a.stride < a.n_k ? a.stride : a.n_k,
+              a.kv_num_blocks + row);
 }
 
 // ---------------------------------------------------------------------------
@@ -472,15 +488,15 @@ __global__ __launch_bounds__(64 * kFusedRows) void score_select_kernel(ScoreSele
   for (int c = 0; c < C; ++c) {
     const int j = 64 * c + lane;
     const uint32_t v = rk[j < row_len ? j : row_len - 1];  // in bounds, independent reads
-    key[c] = j < a.n_k ? v : 0u;
+    key[c] = j < a.n_k ? v : kPastKey;
   }
   const uint32_t samp[2] = {rk[sample_block(lane, a.n_k)], rk[sample_block(64 + lane, a.n_k)]};
   const int64_t r = bh * a.n_q + i;
   const int kk = a.budget.k[(int)(bh % a.heads)];
   // the row's own LDS keys are in registers now: their space holds the
   // bracketed candidates (at most min(n_k, 64 kSelCand) of them)
-  const SelRule rule = kk > 0 ? rule_sampled<C>(key, kk, a.n_sel, samp, rk, lane) : SelRule{0xffffffffu, 0u};
-  emit_row<C>(key, a.n_k, rule, lane, a.kv_indices + r * a.stride, a.kv_num_blocks + r);
+  const SelRule rule = kk > 0 ? rule_sampled<C, false>(key, kk, a.n_sel, samp, rk, lane) : SelRule{0xffffffffu, 0u};
+  emit_row<C>(key, rule, lane, a.kv_indices + r * a.stride, a.stride < a.n_k ? a.stride : a.n_k, a.kv_num_blocks + r);
 }
 
 size_t score_select_lds_bytes(int n_k) { return (size_t)kFusedRows * ((n_k + 15) / 16 * 16) * sizeof(uint32_t); }
@@ -509,11 +525,18 @@ hipError_t launch_score_select(const ScoreSelectArgs& a, hipStream_t stream) {
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
   const int64_t grid = (a.rows + kSelWaves - 1) / kSelWaves;
   if (grid == 0) return hipSuccess;
-  if (a.n_k <= 512) select_reg_kernel<8><<<grid, 64 * kSelWaves, 0, stream>>>(a);
-  else if (a.n_k <= 1024) select_reg_kernel<16><<<grid, 64 * kSelWaves, 0, stream>>>(a);
-  else if (a.n_k <= 1536) select_reg_kernel<24><<<grid, 64 * kSelWaves, 0, stream>>>(a);
-  else if (a.n_k <= 2304) select_reg_kernel<36><<<grid, 64 * kSelWaves, 0, stream>>>(a);
-  else if (a.n_k <= kSelRegMaxBlocks) select_reg_kernel<kSelRegMaxBlocks / 64><<<grid, 64 * kSelWaves, 0, stream>>>(a);
+  // The smallest instance that holds the row: a chunk past n_k still costs its
+  // instructions (24 heads, 188 blocks: the whole selector 26.4 us at C = 8, 24.2
+  // at C = 4).  Up to 8 keys a lane the search of the whole row costs no more than
+  // the sample and its sort (51.4 us at 485 blocks, 52.6 with the sample).
+  if (a.n_k <= 64) select_reg_kernel<1, false><<<grid, 64 * kSelWaves, 0, stream>>>(a);
+  else if (a.n_k <= 256) select_reg_kernel<4, false><<<grid, 64 * kSelWaves, 0, stream>>>(a);
+  else if (a.n_k <= 512) select_reg_kernel<8, false><<<grid, 64 * kSelWaves, 0, stream>>>(a);
+  else if (a.n_k <= 1024) select_reg_kernel<16, true><<<grid, 64 * kSelWaves, 0, stream>>>(a);
+  else if (a.n_k <= 1536) select_reg_kernel<24, true><<<grid, 64 * kSelWaves, 0, stream>>>(a);
+  else if (a.n_k <= 2304) select_reg_kernel<36, true><<<grid, 64 * kSelWaves, 0, stream>>>(a);
+  else if (a.n_k <= kSelRegMaxBlocks)
+    select_reg_kernel<kSelRegMaxBlocks / 64, true><<<grid, 64 * kSelWaves, 0, stream>>>(a);
   else select_kernel<<<grid, 64 * kSelWaves, 0, stream>>>(a);
   return hipGetLastError();
 }

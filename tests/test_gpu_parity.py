@@ -231,6 +231,32 @@ def test_batch_of_two_end_to_end(gpu_lib, split):
             check_output(og[b, h][None], o_ref[None], lg[b, h][None], l_ref[None], what=f"b {b} h {h}")
 
 
+@pytest.mark.parametrize("n_k", [1, 63, 64, 65, 255, 256, 257, 511, 512, 513])
+def test_selector_register_instances(gpu_lib, n_k):
+    """Row lengths around the edges of the register-held instances, with the
+    ragged last block and every third block a copy of block 0 (tied scores): on
+    the GPU's own fp32 scores the lists are exactly the oracle's choice."""
+    w = TINY.with_(name=f"reg-{n_k}", heads=2, head_dim=64, lq=64 * 5 + 3, l_ref=64, l_text=0, seed=53 + n_k)
+    lk = 64 * n_k - 7
+    _say(f"[selector] {n_k} key blocks, tied scores")
+    rng = np.random.default_rng(w.seed)
+    as_bf16 = lambda x: (x.astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    qb_ = as_bf16(rng.standard_normal((1, w.heads, w.lq, w.head_dim)))
+    kb_ = as_bf16(rng.standard_normal((1, w.heads, lk, w.head_dim)))
+    for j in range(3, lk // 64, 3):
+        kb_[:, :, 64 * j:64 * j + 64] = kb_[:, :, :64]
+    keep = [(100, 130), (lk - 200, lk - 190)] if n_k > 8 else []
+    for rho in (0.1, 0.4, 1.0):
+        num, idx, scores, _, _ = _run_selector(gpu_lib, w, to_dev(qb_), to_dev(kb_), keep, rho)
+        s = scores.cpu().numpy()[0]
+        keep_set = O.keep_blocks(keep, lk, w.block)
+        sel = O.selectable_blocks(keep_set, lk, w.block)
+        kk = O.budget_k(rho, len(sel))
+        for h, rows in enumerate(lists_from_device(num, idx)[0]):
+            for i, row in enumerate(rows):
+                assert row == sorted(set(keep_set) | set(O.topk_idx(s[h, i].astype(np.float64), sel, kk))), (h, i)
+
+
 def test_selector_everything_forced(gpu_lib):
     """n_sel = 0: every list is exactly J_keep."""
     import torch
