@@ -101,100 +101,135 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// score: one work-group per (bh, 64 query blocks, 64 key blocks) tile of S,
-// four waves, each a 32 x 32 sub-tile on v_mfma_f32_32x32x16_f16.  Every
-// thread issues all of its global loads (its row's 16-byte pieces of the hi and
-// lo parts, for all of D) at once, so a work-group waits for memory once; D
-// then goes through LDS in chunks of SKC columns, each LDS row holding the
-// chunk's hi then lo values of one pooled row, padded to 144 bytes: 16
+// score: one work-group per (bh, 64 query blocks, `run` consecutive tiles of 64
+// key blocks), four waves, each a 32 x 32 sub-tile of every tile on
+// v_mfma_f32_32x32x16_f16.  A wave keeps its 32 query rows' operands (all of D,
+// hi and lo) in registers, loaded from memory once; a key tile is staged whole
+// in LDS while the next one's loads are in flight.
+//
+// LDS rows hold a pooled row's D hi then D lo values, padded by 16 bytes: 16
 // consecutive rows read at one 16-byte offset then fall on 16 disjoint groups
 // of four banks.
 //
 // MFMA operands (lane l, h = l / 32): A[m][k] = qbar[m = l % 32][d],
 // B[k][n] = kbar[n = l % 32][d], k = 8 h + i over the lane's 8 fp16 values at
 // d = 16 s + 8 h + i of k-step s.  C[m][n] sits at accumulator a with
-// n = l % 32, m = 8 (a / 4) + 4 h + (a % 4).
+// n = l % 32, m = 8 (a / 4) + 4 h + (a % 4).  Rows past the end of either
+// operand repeat its last one: they reach only elements that are not stored.
+//
+// 24 heads, 1,125 x 2,259 blocks: 81 us, with S written at 3.0 TB/s (50 us at the
+// copy rate; the matrix instructions alone are 22).  One tile per work-group with
+// both operands read from LDS took 93: twice the LDS reads per product and no
+// load in flight under them.  Operands read straight from memory in MFMA order
+// (32-byte pieces of 32 rows) instead of through LDS: 91.
 // ---------------------------------------------------------------------------
-constexpr int ST = 64;   // tile edge (query blocks and key blocks)
-constexpr int SKC = 32;  // D chunk
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+constexpr int ST = 64;  // tile edge (query blocks and key blocks)
 
 template <int D>
-__global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
-  constexpr int RB = 144;  // padded LDS row (bytes): SKC hi + SKC lo fp16
-  __shared__ __attribute__((aligned(16))) unsigned char qs[ST * RB];
-  __shared__ __attribute__((aligned(16))) unsigned char ks[ST * RB];
-  __shared__ int qe[ST], ke[ST];
+__global__ __launch_bounds__(256) void score_kernel(ScoreArgs a, int run) {
+  constexpr int RB = 4 * D + 16;     // padded LDS row (bytes)
+  constexpr int NP = D / 32;         // 16-byte pieces of a row per loading thread
+  constexpr int NS = D / 16;         // k-steps
+  __shared__ __attribute__((aligned(16))) unsigned char ts[ST * RB];
+  __shared__ __attribute__((aligned(16))) int qe[ST];
   const int tiles_i = (a.n_q + ST - 1) / ST;
   const int tiles_j = (a.n_k + ST - 1) / ST;
+  const int runs = (tiles_j + run - 1) / run;
   // consecutive tiles (one head's, key tiles fastest) on the same XCD, whose
   // L2 then holds that head's pooled blocks
   int64_t wg = xcd_linear(blockIdx.x, (int64_t)gridDim.x);
-  const int tj = (int)(wg % tiles_j);
-  wg /= tiles_j;
+  const int tj0 = (int)(wg % runs) * run;
+  const int tj1 = tj0 + run < tiles_j ? tj0 + run : tiles_j;
+  wg /= runs;
   const int ti = (int)(wg % tiles_i);
   const int64_t bh = wg / tiles_i;
-  const int i0 = ti * ST, j0 = tj * ST;
+  const int i0 = ti * ST;
 
   const int t = threadIdx.x;
   const int wave = t / 64, lane = t % 64, l32 = lane % 32, h = lane / 32;
   const int wq = wave / 2, wk = wave % 2;  // the wave's 32 x 32 sub-tile
-  // loader: thread t stages row lr, 16-byte piece lc of the chunk's hi and lo
-  // parts.  Rows past the end re-read a valid row and are zeroed when staged.
-  const int lr = t / 4, lc = t % 4;
-  const bool q_ok = i0 + lr < a.n_q, k_ok = j0 + lr < a.n_k;
-  const uint16_t* const qrow = a.q_bar + (bh * a.n_q + (q_ok ? i0 + lr : 0)) * (2 * D) + 8 * lc;
-  const uint16_t* const krow = a.k_bar + (bh * a.n_k + (k_ok ? j0 + lr : 0)) * (2 * D) + 8 * lc;
-  auto ld = [](const uint16_t* p) { return *reinterpret_cast<const uint4*>(p); };
-  // element-wise (a select of whole uint4 values goes through scratch memory)
-  auto keep_if = [](bool ok, uint4 v) {
-    return make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
-  };
-  constexpr int NC = D / SKC;
-  uint4 qh[NC], ql[NC], kh[NC], kl[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    qh[c] = ld(qrow + c * SKC);
-    ql[c] = ld(qrow + D + c * SKC);
-    kh[c] = ld(krow + c * SKC);
-    kl[c] = ld(krow + D + c * SKC);
-  }
-  if (t < ST) qe[t] = i0 + t < a.n_q ? a.q_exp[bh * a.n_q + i0 + t] : 0;
-  else if (t < 2 * ST) ke[t - ST] = j0 + t - ST < a.n_k ? a.k_exp[bh * a.n_k + j0 + t - ST] : 0;
 
-  f32x16 acc;
+  // loader: eight threads read 128 contiguous bytes of a row; thread t has
+  // pieces t % 8 + 8 p of rows t / 8 and t / 8 + 32, p turned by one in odd rows
+  // so that a pair of rows is written to different banks
+  const int lr = t / 8, odd = lr % 2;
+  u32x4 v[2][NP];
+  auto load = [&](const uint16_t* base, int r0, int n) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    for (int r = 0; r < 2; ++r) {
+      const int i = r0 + lr + 32 * r < n ? r0 + lr + 32 * r : n - 1;
+      const uint16_t* row = base + (int64_t)i * (2 * D) + 8 * (t % 8);
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    if (c > 0) __syncthreads();  // the previous chunk's reads are done
-    *reinterpret_cast<uint4*>(qs + lr * RB + 16 * lc) = keep_if(q_ok, qh[c]);
-    *reinterpret_cast<uint4*>(qs + lr * RB + 64 + 16 * lc) = keep_if(q_ok, ql[c]);
-    *reinterpret_cast<uint4*>(ks + lr * RB + 16 * lc) = keep_if(k_ok, kh[c]);
-    *reinterpret_cast<uint4*>(ks + lr * RB + 64 + 16 * lc) = keep_if(k_ok, kl[c]);
-    __syncthreads();
-    const unsigned char* qa = qs + (wq * 32 + l32) * RB + 16 * h;
-    const unsigned char* kc = ks + (wk * 32 + l32) * RB + 16 * h;
-#pragma unroll
-    for (int s = 0; s < SKC / 16; ++s) {
-      const f16x8 ah = *reinterpret_cast<const f16x8*>(qa + 32 * s);
-      const f16x8 al = *reinterpret_cast<const f16x8*>(qa + 64 + 32 * s);
-      const f16x8 bh_ = *reinterpret_cast<const f16x8*>(kc + 32 * s);
-      const f16x8 bl = *reinterpret_cast<const f16x8*>(kc + 64 + 32 * s);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh_, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh_, acc, 0, 0, 0);
+      for (int p = 0; p < NP; ++p) v[r][p] = *reinterpret_cast<const u32x4*>(row + 64 * (p ^ odd));
     }
+  };
+  auto stage = [&] {
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+        *reinterpret_cast<u32x4*>(ts + (lr + 32 * r) * RB + 16 * (t % 8) + 128 * (p ^ odd)) = v[r][p];
+  };
+  const uint16_t* const kb = a.k_bar + bh * a.n_k * (2 * D);
+  const int32_t* const kx = a.k_exp + bh * a.n_k;
+  auto key_exp = [&](int tj) {
+    const int j = tj * ST + wk * 32 + l32;
+    return kx[j < a.n_k ? j : a.n_k - 1];
+  };
+
+  load(a.q_bar + bh * a.n_q * (2 * D), i0, a.n_q);
+  if (t < ST) qe[t] = a.q_exp[bh * a.n_q + (i0 + t < a.n_q ? i0 + t : a.n_q - 1)];
+  stage();
+  load(kb, tj0 * ST, a.n_k);
+  int ek = key_exp(tj0);
+  __syncthreads();
+  const unsigned char* const qr = ts + (wq * 32 + l32) * RB + 16 * h;
+  f16x8 ah[NS], al[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    ah[s] = *reinterpret_cast<const f16x8*>(qr + 32 * s);
+    al[s] = *reinterpret_cast<const f16x8*>(qr + 2 * D + 32 * s);
   }
 
-  const int j = j0 + wk * 32 + l32;
-  if (j >= a.n_k || keep_block(a.keep, j)) return;  // no barrier below
-  const int ej = ke[wk * 32 + l32];
-  float* scol = a.s + bh * (int64_t)a.n_q * a.s_stride + j;
+  const unsigned char* const kr = ts + (wk * 32 + l32) * RB + 16 * h;
+  const int irow = i0 + wq * 32 + 4 * h;  // the lane's first row of S
+  float* const sbase = a.s + (bh * a.n_q + irow) * a.s_stride;
+  for (int tj = tj0; tj < tj1; ++tj) {
+    __syncthreads();  // the previous tile's reads are done
+    stage();
+    const int ej = ek;
+    __syncthreads();
+    if (tj + 1 < tj1) {
+      load(kb, (tj + 1) * ST, a.n_k);
+      ek = key_exp(tj + 1);
+    }
+
+    f32x16 acc;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int r = wq * 32 + 8 * (e / 4) + 4 * h + (e % 4);
-    const int i = i0 + r;
-    if (i < a.n_q) scol[(int64_t)i * a.s_stride] = a.tau * __builtin_amdgcn_ldexpf(acc[e], qe[r] + ej);
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const f16x8 bh_ = *reinterpret_cast<const f16x8*>(kr + 32 * s);
+      const f16x8 bl = *reinterpret_cast<const f16x8*>(kr + 2 * D + 32 * s);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[s], bh_, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[s], bl, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[s], bh_, acc, 0, 0, 0);
+    }
+
+    const int j = tj * ST + wk * 32 + l32;
+    if (j < a.n_k && !keep_block(a.keep, j)) {
+      float* const scol = sbase + j;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const u32x4 eq = *reinterpret_cast<const u32x4*>(qe + wq * 32 + 8 * g + 4 * h);
+        
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (irow + 8 * g + e < a.n_q)
+            scol[(int64_t)(8 * g + e) * a.s_stride] = a.tau * __builtin_amdgcn_ldexpf(acc[4 * g + e], (int)eq[e] + ej);
+      }
+    }
   }
 }
 
@@ -209,11 +244,21 @@ hipError_t launch_pool(const PoolArgs& a, int d, int block, hipStream_t stream) 
   return hipGetLastError();
 }
 
+// Key tiles per work-group.  A run shares one load of the query operands: 97 us at
+// run 1, 85 at 2, 82 at 3, 80 at 4, 82 at 6 (24 heads, 1,125 x 2,259 blocks).  It is
+// cut so that at least kScoreGroups work-groups remain (three fit a CU).
+constexpr int kScoreRun = 4;
+constexpr int64_t kScoreGroups = 2048;
+
 hipError_t launch_score(const ScoreArgs& a, int d, hipStream_t stream) {
-  const int64_t grid = (int64_t)a.bh * ((a.n_q + ST - 1) / ST) * ((a.n_k + ST - 1) / ST);
-  if (grid == 0) return hipSuccess;
-  if (d == 128) score_kernel<128><<<grid, 256, 0, stream>>>(a);
-  else if (d == 64) score_kernel<64><<<grid, 256, 0, stream>>>(a);
+  const int64_t rows = (int64_t)a.bh * ((a.n_q + ST - 1) / ST);
+  const int64_t tiles_j = (a.n_k + ST - 1) / ST;
+  if (rows == 0 || tiles_j == 0) return hipSuccess;
+  const int64_t fill = rows * tiles_j / kScoreGroups;
+  const int run = (int)(fill < 1 ? 1 : fill > kScoreRun ? kScoreRun : fill);
+  const int64_t grid = rows * ((tiles_j + run - 1) / run);
+  if (d == 128) score_kernel<128><<<grid, 256, 0, stream>>>(a, run);
+  else if (d == 64) score_kernel<64><<<grid, 256, 0, stream>>>(a, run);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -257,6 +257,36 @@ def test_selector_register_instances(gpu_lib, n_k):
                 assert row == sorted(set(keep_set) | set(O.topk_idx(s[h, i].astype(np.float64), sel, kk))), (h, i)
 
 
+@pytest.mark.parametrize("d,heads,n_q,n_k", [
+    (64, 1, 1, 1), (64, 1, 64, 65), (64, 3, 65, 129),           # one key tile per work-group
+    (128, 32, 129, 64 * 22), (64, 32, 129, 64 * 42 + 1),         # just past 2048 tiles; runs of two, a short last one
+    (64, 32, 193, 64 * 49 + 3), (128, 40, 257, 64 * 42 - 5),     # runs of three and of four
+])
+def test_score_runs_match_reference(gpu_lib, d, heads, n_q, n_k):
+    """Scores of every block pair where work-groups take 1 to 4 key tiles, against
+    a float64 product of the means of one-row blocks (all other rows zero), whose
+    pooled values are exact.  Against sum |q k| the two splits and the dropped
+    lo.lo term leave 3 2^-22 and the fp32 sum of 3 D/16 matrix steps, a few
+    roundings each, under 3 2^-20: together below 2^-18."""
+    import torch
+
+    _say(f"[scores] H={heads} {n_q} x {n_k} blocks D={d}")
+    g = torch.Generator(device="cuda").manual_seed(59)
+    rows_q = torch.randn(heads, n_q, d, device="cuda", generator=g).bfloat16()
+    rows_k = torch.randn(heads, n_k, d, device="cuda", generator=g).bfloat16()
+    q = torch.zeros(1, heads, 64 * (n_q - 1) + 1, d, device="cuda", dtype=torch.bfloat16)
+    k = torch.zeros(1, heads, 64 * (n_k - 1) + 1, d, device="cuda", dtype=torch.bfloat16)
+    q[0, :, ::64] = rows_q
+    k[0, :, ::64] = rows_k
+    scores = torch.full((1, heads, n_q, n_k), float("nan"), device="cuda")
+    gpu_lib.sparstar_score_blocks(q, k, 64, 0.5, [], scores=scores)
+    for h in range(heads):
+        a, b = rows_q[h].double() / 64, rows_k[h].double() / 64
+        want, mag = a @ b.T * d ** -0.5, a.abs() @ b.abs().T * d ** -0.5
+        err = (scores[0, h].double() - want).abs()
+        assert (err <= 2.0 ** -18 * mag).all(), (h, float((err / mag).max()))
+
+
 def test_selector_everything_forced(gpu_lib):
     """n_sel = 0: every list is exactly J_keep."""
     import torch
