@@ -848,31 +848,13 @@ static hipError_t launch_merge(const AttnArgs& a, hipStream_t stream) {
 }
 
 template <int D, int BLK, int NW, bool DENSE>
-static hipError_t launch_cfg(const AttnArgs& args, hipStream_t stream) {
-  const int64_t n_g = (args.lq + 32 * NW - 1) / (32 * NW);  // query groups per head
-  if (n_g == 0) return hipSuccess;
-  AttnArgs a = args;
-  // How many XCDs share a (head, range) pair.  One keeps the pair's K/V in one
-  // L2, but an XCD with only a few pairs runs as long as its heads' lists are
-  // (per-head budgets differ).  So a pair is shared until each XCD has four
-  // units, as long as a unit keeps 4,096 query rows (half of what an XCD holds):
-  // 8 heads with budgets from 0.5 to 1.5 of the mean, 21,332 queries, took
-  // 0.56 ms shared by four and 0.71 unshared; 6,413 queries 0.62 and 0.44.  The
-  // units of all pairs have to deal out evenly in any case.
-  const int64_t pairs = (int64_t)a.bh * a.n_splits;
-  auto enough = [&](int bits) {
-    const int64_t units = pairs << bits;
-    return units % 8 == 0 && (units >= 32 || ((n_g * 32 * NW) >> (bits + 1)) < 4096);
-  };
-  a.spread_bits = 0;
-  while (a.spread_bits < 3 && !enough(a.spread_bits)) ++a.spread_bits;
-  const int64_t units = ((pairs << a.spread_bits) + 7) / 8 * 8;
-  const int64_t grid = units * ((n_g + (1 << a.spread_bits) - 1) >> a.spread_bits);
+static hipError_t launch_cfg(const AttnArgs& a, hipStream_t stream) {
+  if (a.grid == 0) return hipSuccess;
   if (a.part_o == nullptr) {
-    attn_fwd_kernel<D, BLK, NW, DENSE, false><<<grid, 64 * NW, 0, stream>>>(a);
+    attn_fwd_kernel<D, BLK, NW, DENSE, false><<<a.grid, 64 * NW, 0, stream>>>(a);
     return hipGetLastError();
   }
-  attn_fwd_kernel<D, BLK, NW, DENSE, true><<<grid, 64 * NW, 0, stream>>>(a);
+  attn_fwd_kernel<D, BLK, NW, DENSE, true><<<a.grid, 64 * NW, 0, stream>>>(a);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   return launch_merge<D, BLK>(a, stream);
 }
@@ -880,12 +862,7 @@ static hipError_t launch_cfg(const AttnArgs& args, hipStream_t stream) {
 template <int D, int BLK>
 static hipError_t launch_mode(const AttnArgs& a, bool dense, hipStream_t stream) {
   if (!dense) return launch_cfg<D, BLK, BLK / 32, false>(a, stream);
-  // 128-row groups, but 64 rows where those would be so few that most CUs stay
-  // idle (1,056 queries of one head: 13.8 us against 15.9), or would pad a
-  // short query sequence by more than a tenth (774 queries of 10 heads: 154 and 158)
-  const int64_t wide = (a.lq + 127) / 128, narrow = (a.lq + 63) / 64, n_wide = wide * a.bh * a.n_splits;
-  if (n_wide <= 64 || (n_wide > 256 && 20 * wide > 11 * narrow)) return launch_cfg<D, BLK, 2, true>(a, stream);
-  return launch_cfg<D, BLK, 4, true>(a, stream);
+  return a.group_rows == 64 ? launch_cfg<D, BLK, 2, true>(a, stream) : launch_cfg<D, BLK, 4, true>(a, stream);
 }
 
 hipError_t launch_attn(const AttnArgs& a, int d, int block, bool dense, hipStream_t stream) {

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/sparstar.h"
+#include "attn_plan.h"
 #include "host_internal.h"
 #include "launch.h"
 
@@ -333,58 +334,17 @@ extern "C" size_t sparstar_attn_workspace_bytes(int B, int H, int64_t Lq, int64_
                                         block_size);
 }
 
-// How an attention call is cut up: key ranges per query block, and the rotation
-// of the lists (AttnArgs).
-struct AttnPlan {
-  int ranges, rotation;
-};
-
-// The number of key ranges R (1, 2, 4 or 8) that minimises an estimate of the
-// call's time, in units of one 32-key tile step with the chip full:
-//   - an item (one query block and range) takes its share of the list plus about
-//     16 steps of fixed work (list scan, Q, first tiles, epilogue) and, with
-//     R > 1, 3 for its partial result and the merge (twice as many steps at
-//     D = 64, whose step is half as long);
-//   - the chip holds 65,536 query rows at D = 128, 98,304 at D = 64 (two, three
-//     waves per SIMD): x rounds of items.  A partly filled last round takes half
-//     an item's time when nearly empty, since the waves left share less;
-//   - K and V of one range beyond about 20 MB lose the L2's reuse between the
-//     items in flight (15%, and 30% more beyond 40 MB).
-// A range keeps at least 256 listed keys.  Against the best R of a sweep over 25
-// shapes (1 to 24 heads, 512 to 72,000 queries, 1,152 to 144,512 keys, both
-// head dims and block sizes, sparse and dense) the estimate's choice is 0.2%
-// slower on average and 1.4% at worst; 16 ranges were never the best.
-// The estimate reads the list length, not the kind of call, so that the dense
-// call and a sparse call whose lists can name every block are cut alike.
-// With several ranges the lists are rotated (attn_fwd.hip) where some cannot name
-// every block and at least eight rounds of items let the work-groups in flight
-// spread out in time (mid-scale call, 11,520 queries: 3.25 ms rotated and 4.01
-// plain at 17 rounds; 6,413 queries and 8 heads: 478 and 476 us at 3).
-static AttnPlan attn_plan(int64_t bh, int64_t nq, int64_t nk, int64_t lk, int d, int block, int64_t list_blocks,
-                          bool may_split) {
-  const double list_keys = double(list_blocks) * block;
-  const double rows = double(bh) * double(nq) * block;
-  const double rows_held = 32768.0 * sparstar::attn_waves_per_simd(d);
-  const double kv_bytes = double(lk) * 4.0 * d;
-  AttnPlan plan{1, 0};
-  double best = 0.0, best_rounds = 0.0;
-  for (int r = 1; r <= 8; r *= 2) {
-    if (r > 1 && (!may_split || list_keys < 256.0 * r)) break;
-    const double rounds = rows * r / rows_held, whole = floor(rounds), part = rounds - whole;
-    const double item = list_keys / 32.0 / r + (r > 1 ? 19.0 : 16.0) * (128.0 / d);
-    double t = item * (whole + (part > 0.0 ? 0.5 + 0.5 * part : 0.0));
-    if (rounds > 1.0) {
-      if (kv_bytes / r > double(20 << 20)) t *= 1.15;
-      if (kv_bytes / r > double(40 << 20)) t *= 1.3;
-    }
-    if (r == 1 || t < best) {
-      best = t;
-      best_rounds = rounds;
-      plan.ranges = r;
-    }
-  }
-  if (plan.ranges > 1 && list_blocks < nk && best_rounds >= 8.0) plan.rotation = int(rows_held) / 8 / block;
-  return plan;
+extern "C" void sparstar_internal_attn_plan(int B, int H, int64_t Lq, int64_t Lk, int D, int block_size,
+                                            int64_t kv_stride, int with_workspace, int64_t* out) {
+  using namespace sparstar;
+  const bool split = with_workspace && attn_workspace_bytes(int64_t(B) * H, ceil_div(Lq, block_size),
+                                                            ceil_div(Lk, block_size), D, block_size) > 0;
+  const AttnPlan p = attn_plan(int64_t(B) * H, Lq, Lk, D, block_size, kv_stride, kv_stride == 0, split);
+  out[0] = p.ranges;
+  out[1] = p.rotation;
+  out[2] = p.group_rows;
+  out[3] = p.spread_bits;
+  out[4] = p.grid;
 }
 
 static int attn_common(const void* q, const void* k, const void* v, int B, int H, int64_t Lq, int64_t Lk, int D,
@@ -431,11 +391,12 @@ static int attn_common(const void* q, const void* k, const void* v, int B, int H
   a.n_k = int(nk);
   a.stride = dense ? 0 : kv_stride;
   a.scale_log2 = float(sc * 1.4426950408889634074);
-  // The dense call lists every key block, so it takes the plan of a full list.
-  const AttnPlan plan =
-      attn_plan(int64_t(B) * H, nq, nk, Lk, D, block_size, dense ? nk : std::min<int64_t>(kv_stride, nk), split);
+  const AttnPlan plan = attn_plan(int64_t(B) * H, Lq, Lk, D, block_size, dense ? 0 : kv_stride, dense, split);
   a.n_splits = plan.ranges;
   a.rotation = plan.rotation;
+  a.group_rows = plan.group_rows;
+  a.spread_bits = plan.spread_bits;
+  a.grid = plan.grid;
   if (plan.ranges > 1) {
     const int64_t rows = int64_t(B) * H * nq * kSplits * block_size;
     char* ws = static_cast<char*>(workspace);

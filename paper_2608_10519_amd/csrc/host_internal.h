@@ -28,3 +28,9 @@ size_t score_pooled_bytes(int B, int H, int64_t Lq, int64_t Lk, int D, int block
 int report_error(int code, const char* msg);
 
 }  // namespace sparstar
+
+// The cut of an attention call (attn_plan.h), for tests: key ranges, rotation,
+// rows per work-group, log2 of the XCDs per (head, range) pair, work-groups.
+// kv_stride 0 is the dense call.
+extern "C" void sparstar_internal_attn_plan(int B, int H, int64_t Lq, int64_t Lk, int D, int block_size,
+                                            int64_t kv_stride, int with_workspace, int64_t out[5]);

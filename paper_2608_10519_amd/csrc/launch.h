@@ -103,7 +103,9 @@ struct AttnArgs {
                       // row sum of the fp32 p, e (the row's power-of-two scale, as a float)
   int n_splits;       // key ranges per query block: 2, 4 or 8 with part_o, else 1
   int rotation;       // work-groups in flight per XCD, for the start of each list; 0: start at its head
-  int spread_bits;    // log2 of the XCDs that share a (head, range) pair (set by the launcher)
+  int spread_bits;    // log2 of the XCDs that share a (head, range) pair
+  int group_rows;     // query rows of a work-group (launcher only)
+  int64_t grid;       // work-groups (launcher only)
 };
 
 // The split workspace holds this many key ranges per query block (attn_plan

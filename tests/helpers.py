@@ -117,3 +117,16 @@ def check_output(o_gpu: np.ndarray, o_ref: np.ndarray, lse_gpu=None, lse_ref=Non
             dl = np.abs(lse_gpu[fin] - lse_ref[fin]).max()
             assert dl <= lse_abs, f"{what}: max |dlse| = {dl:.3e}"
     return float(d.max())
+
+
+def attn_plan(lib, B, H, Lq, Lk, D, block, kv_stride=0, workspace=True):
+    """The library's cut of an attention call (attn_plan.h); kv_stride 0: the dense call."""
+    import ctypes
+    from collections import namedtuple
+
+    if hasattr(lib, "load"):  # the binding rather than the library itself
+        lib = lib.load()
+    out = (ctypes.c_int64 * 5)()
+    i64 = ctypes.c_int64
+    lib.sparstar_internal_attn_plan(B, H, i64(Lq), i64(Lk), D, block, i64(kv_stride), int(workspace), out)
+    return namedtuple("Plan", "ranges rotation group_rows spread_bits grid")(*out)

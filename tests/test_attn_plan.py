@@ -1,0 +1,45 @@
+"""How attention calls are cut up (host code, no GPU): key ranges, rotation,
+rows per work-group and the work-groups launched, as the library plans them."""
+import pytest
+
+from paper_2608_10519_amd import sparstar as S
+from tests.helpers import attn_plan
+
+
+@pytest.fixture(scope="module")
+def lib():
+    return S.load()
+
+
+@pytest.mark.parametrize("bh,lq,d,b,stride", [(1, 64, 128, 64, 9), (3, 200, 64, 64, 0), (7, 4420, 128, 128, 9),
+                                              (5, 3800, 128, 64, 256), (24, 1000, 64, 128, 0), (35, 200, 64, 64, 0),
+                                              (2, 20_001, 128, 64, 40)])
+@pytest.mark.parametrize("ws", [False, True])
+def test_grid_covers_every_item_once(lib, bh, lq, d, b, stride, ws):
+    """The kernel's decode of its work-group id (attn_fwd.hip), over the planned
+    grid, gives every (head, range) pair and query group exactly once."""
+    p = attn_plan(lib, 1, bh, lq, 64 * 700 + 3, d, b, stride, ws)
+    groups, pairs, bits = -(-lq // p.group_rows), bh * p.ranges, p.spread_bits
+    n_u = (groups + (1 << bits) - 1) >> bits
+    seen = set()
+    for block in range(p.grid):
+        ui, gi = divmod(block // 8, n_u)
+        unit = ui * 8 + (block + ui) % 8
+        item = unit >> bits, (gi << bits) + (unit & ((1 << bits) - 1))
+        if item[0] < pairs and item[1] < groups:
+            assert item not in seen
+            seen.add(item)
+    assert len(seen) == pairs * groups
+
+
+def test_plan_without_workspace_or_with_few_blocks_is_one_range(lib):
+    assert attn_plan(lib, 1, 24, 72_000, 144_512, 128, 64, 571, False).ranges == 1
+    assert attn_plan(lib, 1, 24, 72_000, 64 * 15, 128, 64, 0, True).ranges == 1
+
+
+def test_dense_and_full_lists_take_the_same_ranges(lib):
+    for bh, lq, lk, d, b in [(24, 2880, 75_392, 128, 64), (1, 1000, 144_000, 128, 64), (3, 5000, 9000, 64, 128),
+                             (2, 300, 24_616, 64, 64)]:
+        dense = attn_plan(lib, 1, bh, lq, lk, d, b, 0, True)
+        for stride in (-(-lk // b), -(-lk // b) + 50):
+            assert attn_plan(lib, 1, bh, lq, lk, d, b, stride, True).ranges == dense.ranges
