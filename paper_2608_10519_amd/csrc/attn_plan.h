@@ -35,14 +35,19 @@ inline int attn_group_rows(int64_t bh, int64_t lq, int block, bool dense, int ra
 // units, as long as a unit keeps 4,096 query rows (half of what an XCD holds):
 // 8 heads with budgets from 0.5 to 1.5 of the mean, 21,332 queries, took
 // 0.56 ms shared by four and 0.71 unshared; 6,413 queries 0.62 and 0.44.  The
-// units of all pairs have to deal out evenly in any case.
+// units of all pairs have to deal out evenly in any case, but a pair is never
+// shared by more XCDs than it has groups: the work-groups of the empty units
+// return at once, yet count as placed when the dispatcher goes round the CUs
+// (dense call, 35 heads of 200 queries, two groups each: 21.5 us shared by
+// eight, 16.4 by one or two), and eight times as many work-groups as items can
+// pass the launch limit of 2^32 threads.
 inline int attn_spread_bits(int64_t pairs, int64_t groups, int group_rows) {
   auto enough = [&](int bits) {
     const int64_t units = pairs << bits;
     return units % 8 == 0 && (units >= 32 || ((groups * group_rows) >> (bits + 1)) < 4096);
   };
   int bits = 0;
-  while (bits < 3 && !enough(bits)) ++bits;
+  while (bits < 3 && (int64_t(1) << bits) < groups && !enough(bits)) ++bits;
   return bits;
 }
 

@@ -43,3 +43,22 @@ def test_dense_and_full_lists_take_the_same_ranges(lib):
         dense = attn_plan(lib, 1, bh, lq, lk, d, b, 0, True)
         for stride in (-(-lk // b), -(-lk // b) + 50):
             assert attn_plan(lib, 1, bh, lq, lk, d, b, stride, True).ranges == dense.ranges
+
+
+@pytest.mark.parametrize("bh", [1, 3, 8, 25, 35, 1001])
+@pytest.mark.parametrize("lq", [1, 64, 65, 200, 300, 513, 4420])
+@pytest.mark.parametrize("b,stride,ws", [(64, 0, False), (64, 9, False), (128, 9, True), (64, 0, True)])
+def test_few_empty_work_groups(lib, bh, lq, b, stride, ws):
+    """Empty work-groups (past a unit's last group) stay fewer than the items,
+    apart from the padding to eight units."""
+    p = attn_plan(lib, 1, bh, lq, 64 * 30, 64, b, stride, ws)
+    groups = -(-lq // p.group_rows)
+    assert p.grid <= 2 * bh * p.ranges * groups + 8 * (-(-groups >> p.spread_bits))
+
+
+def test_many_short_heads_fit_one_launch(lib):
+    """An odd number of heads beyond 4 million, one query each: 537 million
+    threads in items, well inside the launch limit of 2^32 threads."""
+    for stride in (0, 1):
+        p = attn_plan(lib, 1, (1 << 22) + 1, 1, 1, 64, 64, stride, False)
+        assert p.grid * 2 * p.group_rows < 1 << 32
