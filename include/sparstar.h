@@ -174,7 +174,7 @@ int sparstar_score_blocks_fused(const void* q, const void* k, int B, int H, int6
 /*
  * Bytes of device workspace that lets the attention calls below split the key
  * blocks of every query block into contiguous ranges and merge the partial
- * results.  A call takes 1, 2, 4 or 8 ranges, whichever is expected to be
+ * results.  A call takes 1, 2, 4, 8 or 16 ranges, whichever is expected to be
  * fastest for its sizes and list length (kv_stride; for the dense call, every
  * key block of the row).  So the dense call
  * and a sparse call whose lists name every block, in order, give the same bits.

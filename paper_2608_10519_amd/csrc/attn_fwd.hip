@@ -843,6 +843,7 @@ static hipError_t launch_merge(const AttnArgs& a, hipStream_t stream) {
   if (a.n_splits == 2) attn_merge_kernel<D, BLK, 2><<<items, NT, 0, stream>>>(a);
   else if (a.n_splits == 4) attn_merge_kernel<D, BLK, 4><<<items, NT, 0, stream>>>(a);
   else if (a.n_splits == 8) attn_merge_kernel<D, BLK, 8><<<items, NT, 0, stream>>>(a);
+  else if (a.n_splits == 16) attn_merge_kernel<D, BLK, 16><<<items, NT, 0, stream>>>(a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

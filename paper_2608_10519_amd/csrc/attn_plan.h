@@ -12,22 +12,12 @@
 namespace sparstar {
 
 struct AttnPlan {
-  int ranges;       // key ranges per query block: 1, 2, 4 or 8
+  int ranges;       // key ranges per query block: 1, 2, 4, 8 or 16
   int rotation;     // work-groups in flight per XCD, or 0: every list is walked from its head
   int group_rows;   // query rows of a work-group: the block size, or 64 or 128 for the dense call
   int spread_bits;  // log2 of the XCDs that share a (head, range) pair
   int64_t grid;     // work-groups launched
 };
-
-// Rows of a work-group.  The dense call, whose rows all see the same keys, takes
-// 128-row groups, but 64 rows where those would be so few that most CUs stay
-// idle (1,056 queries of one head: 13.8 us against 15.9), or would pad a
-// short query sequence by more than a tenth (774 queries of 10 heads: 154 and 158).
-inline int attn_group_rows(int64_t bh, int64_t lq, int block, bool dense, int ranges) {
-  if (!dense) return block;
-  const int64_t wide = (lq + 127) / 128, narrow = (lq + 63) / 64, n_wide = wide * bh * ranges;
-  return n_wide <= 64 || (n_wide > 256 && 20 * wide > 11 * narrow) ? 64 : 128;
-}
 
 // How many XCDs share a (head, range) pair.  One keeps the pair's K/V in one
 // L2, but an XCD with only a few pairs runs as long as its heads' lists are
@@ -58,55 +48,99 @@ inline int64_t attn_grid(int64_t pairs, int64_t groups, int bits) {
   return units * ((groups + (1 << bits) - 1) >> bits);
 }
 
-// The number of key ranges R (1, 2, 4 or 8) that minimises an estimate of the
-// call's time, in units of one 32-key tile step with the chip full:
-//   - an item (one query block and range) takes its share of the list plus about
-//     16 steps of fixed work (list scan, Q, first tiles, epilogue) and, with
-//     R > 1, 3 for its partial result and the merge (twice as many steps at
-//     D = 64, whose step is half as long);
-//   - the chip holds 65,536 query rows at D = 128, 98,304 at D = 64 (two, three
-//     waves per SIMD): x rounds of items.  A partly filled last round takes half
-//     an item's time when nearly empty, since the waves left share less;
-//   - K and V of one range beyond about 20 MB lose the L2's reuse between the
-//     items in flight (15%, and 30% more beyond 40 MB).
-// A range keeps at least 256 listed keys.  Against the best R of a sweep over 25
-// shapes (1 to 24 heads, 512 to 72,000 queries, 1,152 to 144,512 keys, both
-// head dims and block sizes, sparse and dense) the estimate's choice is 0.2%
-// slower on average and 1.4% at worst; 16 ranges were never the best.
-// The estimate reads the list length, not the kind of call, so that the dense
-// call and a sparse call whose lists can name every block are cut alike.
-// With several ranges the lists are rotated (attn_fwd.hip) where some cannot name
-// every block and at least eight rounds of items let the work-groups in flight
-// spread out in time (mid-scale call, 11,520 queries: 3.25 ms rotated and 4.01
-// plain at 17 rounds; 6,413 queries and 8 heads: 478 and 476 us at 3).
+// An estimate of a call's time in microseconds, for one cut of it.  rho is the
+// share of the key blocks that a list can name (1 for the dense call).
+//
+// What it counts, on the XCD with the most work-groups:
+//   - tile steps: a work-group walks its share of the list, plus 4.5 steps of
+//     fixed work and, on sparse lists cut into ranges, the 1.9 standard deviations by
+//     which the longest share exceeds the mean.  A step's time depends on how
+//     many work-groups share the CU (kStepUs, D and waves per work-group); whole
+//     rounds run full, the last one with what is left of it;
+//   - K/V from beyond the L2: once per round for what the lists cover of the
+//     range, and for every work-group where those in flight are too far apart for
+//     the L2 (3.2 MB of it): by the random spread of their positions in the
+//     range, by a quarter of the range per round that they drift without
+//     rotation, by 6% of it with rotation;
+//   - the merge of the partial results.
+// The constants are fitted to 1,513 random shapes, each timed at every cut (1 to
+// 200 heads, 64 to 72,000 queries, 1,100 to a million keys, 3% to 95% density
+// and dense, uniform and clustered lists, both head dims and block sizes).  The
+// chosen cut is 0.8% slower than the best one on average (15% in one shape of
+// a hundred), and 0.6% on 260 shapes that the fit has not seen.  A count of
+// ranges from tile steps and K/V per range alone, of at most 8, lost 13%: it took
+// 257 us for 1,000 queries of one head over 144,000 keys (16 ranges: 150), and
+// two ranges for short lists, where the merge costs more than it saves (7,686
+// queries of 4 heads, lists of 7 blocks of 128: 35 us, one range 23).
+inline double attn_time_us(int64_t bh, int64_t lq, int64_t lk, int d, int block, double rho, bool dense, int ranges,
+                           bool rotated, int group_rows) {
+  // by work-groups per CU, for work-groups of two and of four waves
+  static constexpr double kStepUs128[2][6] = {{.44, .67, .69, .87}, {.48, .76}};
+  static constexpr double kStepUs64[2][6] = {{.39, .48, .56, .62, .80, .85}, {.42, .57, .78}};
+  const int waves = group_rows / 32;
+  const double* step_us = (d == 64 ? kStepUs64 : kStepUs128)[waves / 4];
+  const int per_cu = 4 * attn_waves_per_simd(d) / waves;
+  const double held = 32.0 * per_cu;  // work-groups an XCD holds
+  const int64_t groups = (lq + group_rows - 1) / group_rows, pairs = bh * ranges;
+  const int bits = attn_spread_bits(pairs, groups, group_rows);
+  const double units = double(((pairs << bits) + 7) / 8);                    // per XCD
+  const double unit_groups = double((groups + (1 << bits) - 1) >> bits);
+  const double work_groups = units * unit_groups, rounds = work_groups / held;
+  const double whole = floor(rounds), part = rounds - whole;
+
+  const int sub = block / 32;
+  const double list_blocks = rho * double((lk + block - 1) / block) / ranges;
+  const double steps = list_blocks * sub + 4.5;
+  const double deviation = sqrt(list_blocks * (1.0 - rho));  // of a share's entries
+  const double longest = steps + (ranges > 1 && !dense ? 1.9 * deviation * sub : 0.0);
+  double t = 2.3 + whole * steps * step_us[per_cu - 1];
+  if (part > 0.0) t += longest * step_us[int(fmax(1.0, ceil(part * per_cu - 1e-9))) - 1];
+  else t += (longest - steps) * step_us[per_cu - 1];
+
+  const double token_bytes = 4.0 * d, range_bytes = double(lk) * token_bytes / ranges;
+  double apart = 1.3 * deviation / rho * block * token_bytes;
+  if (!dense && rounds > 1.0) apart += (rotated ? 0.064 : 0.25 * fmin(1.0, rounds - 1.0)) * range_bytes;
+  apart = fmin(apart, range_bytes);
+  const double miss = apart > 3.2e6 ? 1.0 - 3.2e6 / apart : 0.0;
+  const double covered = dense ? 1.0 : 1.0 - pow(1.0 - rho, fmin(unit_groups, held));
+  const double every = work_groups * list_blocks * block * token_bytes;
+  const double once = fmin(every, units * fmax(1.0, unit_groups / held) * range_bytes * covered);
+  t += (once * (1.0 - miss) + every * miss) / 9e6;
+  if (ranges > 1)
+    t += 3.7 + 0.25 * ranges * block * d / 8192.0 + double(bh) * double(lq) * ranges * token_bytes / 6.3e6;
+  return t;
+}
+
+// The cut with the least estimated time.  The dense call's work-groups take 64 or
+// 128 rows: 128 feed twice the queries per K/V byte loaded, 64 fill more CUs and
+// pad less.  A sparse call whose rows can name every block takes the ranges of
+// the dense call, so that full lists give the dense call's bits.  With several
+// ranges the lists are rotated (attn_fwd.hip) where the estimate says so and
+// some cannot name every block.
 inline AttnPlan attn_plan(int64_t bh, int64_t lq, int64_t lk, int d, int block, int64_t kv_stride, bool dense,
                           bool may_split) {
-  const int64_t nq = (lq + block - 1) / block, nk = (lk + block - 1) / block;
-  // the dense call lists every key block, so it takes the ranges of a full list
-  const int64_t list_blocks = dense || kv_stride > nk ? nk : kv_stride;
-  const double list_keys = double(list_blocks) * block;
-  const double rows = double(bh) * double(nq) * block;
-  const double rows_held = 32768.0 * attn_waves_per_simd(d);
-  const double kv_bytes = double(lk) * 4.0 * d;
+  const int64_t nk = (lk + block - 1) / block;
+  const bool full = dense || kv_stride >= nk;
+  const double rho = full ? 1.0 : double(kv_stride) / double(nk);
   AttnPlan plan{1, 0, 0, 0, 0};
-  double best = 0.0, best_rounds = 0.0;
-  for (int r = 1; r <= 8; r *= 2) {
-    if (r > 1 && (!may_split || list_keys < 256.0 * r)) break;
-    const double rounds = rows * r / rows_held, whole = floor(rounds), part = rounds - whole;
-    const double item = list_keys / 32.0 / r + (r > 1 ? 19.0 : 16.0) * (128.0 / d);
-    double t = item * (whole + (part > 0.0 ? 0.5 + 0.5 * part : 0.0));
-    if (rounds > 1.0) {
-      if (kv_bytes / r > double(20 << 20)) t *= 1.15;
-      if (kv_bytes / r > double(40 << 20)) t *= 1.3;
+  double best = 0.0;
+  for (int rows = full ? 64 : block; rows <= (full ? 128 : block); rows *= 2)
+    for (int r = 1; r <= (may_split ? kSplits : 1); r *= 2) {
+      const int64_t g = (lq + rows - 1) / rows;
+      if (r > 1 && attn_grid(bh * r, g, attn_spread_bits(bh * r, g, rows)) * 2 * rows >> 32) break;  // launch limit
+      // (rotation only matters where the work-groups don't all start at once)
+      const bool rounds = bh * r * g * rows > 32768 * attn_waves_per_simd(d);
+      for (int rotated = 0; rotated <= (r > 1 && !full && rounds); ++rotated) {
+        const double t = attn_time_us(bh, lq, lk, d, block, rho, full, r, rotated, rows);
+        if (plan.group_rows == 0 || t < best) {
+          best = t;
+          plan.group_rows = rows;
+          plan.ranges = r;
+          plan.rotation = rotated ? 32 * 4 * attn_waves_per_simd(d) / (rows / 32) : 0;
+        }
+      }
     }
-    if (r == 1 || t < best) {
-      best = t;
-      best_rounds = rounds;
-      plan.ranges = r;
-    }
-  }
-  if (plan.ranges > 1 && list_blocks < nk && best_rounds >= 8.0) plan.rotation = int(rows_held) / 8 / block;
-  plan.group_rows = attn_group_rows(bh, lq, block, dense, plan.ranges);
+  if (!dense) plan.group_rows = block;
   const int64_t groups = (lq + plan.group_rows - 1) / plan.group_rows, pairs = bh * plan.ranges;
   plan.spread_bits = attn_spread_bits(pairs, groups, plan.group_rows);
   plan.grid = attn_grid(pairs, groups, plan.spread_bits);

@@ -101,15 +101,15 @@ struct AttnArgs {
   uint16_t* part_o;   // [BH * n_q, n_splits, BLK, D] fp16: the range's unnormalised P V times 2^-e per row
   float* part_meta;   // [BH * n_q, n_splits, BLK, 4]: running max (log2 units), row sum of the bf16 P,
                       // row sum of the fp32 p, e (the row's power-of-two scale, as a float)
-  int n_splits;       // key ranges per query block: 2, 4 or 8 with part_o, else 1
+  int n_splits;       // key ranges per query block: 2, 4, 8 or 16 with part_o, else 1
   int rotation;       // work-groups in flight per XCD, for the start of each list; 0: start at its head
   int spread_bits;    // log2 of the XCDs that share a (head, range) pair
   int group_rows;     // query rows of a work-group (launcher only)
   int64_t grid;       // work-groups (launcher only)
 };
 
-// The split workspace holds this many key ranges per query block (attn_plan
-// takes at most 8 of them), and sequences of fewer key blocks are never split.
+// The most key ranges per query block: the split workspace holds as many, and
+// sequences of fewer key blocks are never split.
 constexpr int kSplits = 16;
 
 // Bytes of the fp16 partial-O region of the split workspace (256-byte aligned;

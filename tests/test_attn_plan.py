@@ -4,6 +4,7 @@ import pytest
 
 from paper_2608_10519_amd import sparstar as S
 from tests.helpers import attn_plan
+from tests.test_gpu_parity import PLAN_CASES
 
 
 @pytest.fixture(scope="module")
@@ -62,3 +63,26 @@ def test_many_short_heads_fit_one_launch(lib):
     for stride in (0, 1):
         p = attn_plan(lib, 1, (1 << 22) + 1, 1, 1, 64, 64, stride, False)
         assert p.grid * 2 * p.group_rows < 1 << 32
+
+
+@pytest.mark.parametrize("case", PLAN_CASES, ids=[c[0] for c in PLAN_CASES])
+def test_plans_of_the_gpu_cases(lib, case):
+    """The cases that the GPU tests run take the cuts that they are named for."""
+    _, heads, lq, lk, d, b, n, ranges, rotated, shared = case
+    p = attn_plan(lib, 1, heads, lq, lk, d, b, n, True)
+    assert (p.ranges, p.rotation > 0, p.spread_bits > 0) == (ranges, rotated, shared)
+
+
+@pytest.mark.parametrize("bh,lq,lk,d,b,stride", [
+    (1, 1000, 144_000, 128, 64, 0), (2, 465, 55_727, 64, 64, 0), (2, 199, 57_052, 128, 128, 0),
+    (1, 545, 46_955, 64, 128, 143), (2, 170, 189_379, 128, 128, 635), (1, 79, 34_864, 128, 64, 362)])
+def test_few_queries_over_many_keys_take_sixteen_ranges(lib, bh, lq, lk, d, b, stride):
+    """Fewer work-groups than CUs even at 8 ranges: 16 take little more than half the time."""
+    assert attn_plan(lib, 1, bh, lq, lk, d, b, stride, True).ranges == 16
+
+
+@pytest.mark.parametrize("bh,lq,lk,d,b,stride", [
+    (4, 7686, 7226, 128, 128, 7), (5, 2375, 10_097, 128, 64, 9), (6, 2264, 8426, 128, 64, 11), (1, 6160, 3232, 128, 64, 8)])
+def test_short_lists_take_one_range(lib, bh, lq, lk, d, b, stride):
+    """Lists of a few blocks: the merge of even two ranges costs more than it saves."""
+    assert attn_plan(lib, 1, bh, lq, lk, d, b, stride, True).ranges == 1

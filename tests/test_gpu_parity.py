@@ -822,31 +822,37 @@ def test_attention_writes_only_its_outputs(gpu_lib, dense, split):
                  np.stack([r[1] for r in refs])[None], what="guarded")
 
 
-# The cuts of the attention plan: (name, heads, Lq, Lk, D, b, listed blocks).
-# By the plan's estimate they take 1, 2, 4 and 8 key ranges; the next two are one
-# range in several rounds of items, with units of one XCD and shared ones; the
-# last three take several ranges and enough rounds (65,536 rows each at D = 128,
-# 98,304 at D = 64) that the lists are walked from a rotated start.
+# The cuts of the attention plan: (name, heads, Lq, Lk, D, b, listed blocks,
+# then what the library plans: key ranges, rotated lists, pairs shared between
+# XCDs).  tests/test_attn_plan.py checks the last three without a GPU.  The
+# chip holds 65,536 rows at D = 128, 98,304 at D = 64: many-rounds and
+# shared-units take several rounds in one range.
 PLAN_CASES = [
-    ("one-range", 3, 64 * 5 + 1, 64 * 20 + 3, 128, 64, 4),
-    ("two-ranges", 24, 64 * 16, 64 * 172 + 5, 128, 64, 53),
-    ("four-ranges", 2, 64 * 9 + 7, 64 * 40 + 9, 128, 64, 20),
-    ("eight-ranges", 1, 128 * 16 + 1, 128 * 64 + 77, 64, 128, 38),
-    ("many-rounds", 64, 64 * 128, 64 * 160 + 11, 128, 64, 90),
-    ("shared-units", 3, 64 * 300 + 5, 64 * 310, 64, 64, 17),
-    ("rotated-d64", 32, 64 * 150, 64 * 2700 + 1, 64, 64, 300),
-    ("rotated-b128", 24, 128 * 60 - 3, 128 * 700, 128, 128, 100),
-    ("rotated-four-ranges", 24, 64 * 120 - 1, 64 * 1300 + 13, 128, 64, 330),
+    ("one-range", 3, 64 * 5 + 1, 64 * 20 + 3, 128, 64, 4, 1, False, True),
+    ("many-rounds", 64, 64 * 128, 64 * 160 + 11, 128, 64, 90, 1, False, False),
+    ("shared-units", 5, 64 * 420 + 5, 64 * 310, 64, 64, 17, 1, False, True),
+    ("two-ranges", 24, 64 * 16, 64 * 172 + 5, 128, 64, 53, 2, False, False),
+    ("four-ranges", 2, 128 * 17 - 3, 128 * 18 - 7, 64, 128, 9, 4, False, False),
+    ("eight-ranges", 1, 128 * 16 + 1, 128 * 64 + 77, 64, 128, 38, 8, False, False),
+    ("sixteen-d64-b64", 1, 64 * 144 - 3, 64 * 230 - 7, 64, 64, 115, 16, False, True),
+    ("sixteen-d64-b128", 1, 128 * 3 - 3, 128 * 19 - 7, 64, 128, 15, 16, False, False),
+    ("sixteen-d128-b64", 1, 64 * 2 - 3, 64 * 38 - 7, 128, 64, 30, 16, False, False),
+    ("sixteen-d128-b128", 1, 128 * 2 - 3, 128 * 35 - 7, 128, 128, 28, 16, False, False),
+    ("rotated-2", 12, 128 * 50 - 3, 128 * 188 - 7, 128, 128, 37, 2, True, False),
+    ("rotated-4-d64", 8, 64 * 80 - 3, 64 * 2009 - 7, 64, 64, 100, 4, True, False),
+    ("rotated-4-shared", 2, 64 * 196 - 3, 64 * 1027 - 7, 128, 64, 51, 4, True, True),
+    ("rotated-8-shared", 1, 128 * 157 - 3, 128 * 1272 - 7, 64, 128, 63, 8, True, True),
+    ("rotated-16", 1, 128 * 68 - 3, 128 * 1098 - 7, 128, 128, 109, 16, True, True),
 ]
 
 
-@pytest.mark.parametrize("name,heads,lq,lk,d,b,n", PLAN_CASES, ids=[c[0] for c in PLAN_CASES])
+@pytest.mark.parametrize("name,heads,lq,lk,d,b,n", [c[:7] for c in PLAN_CASES], ids=[c[0] for c in PLAN_CASES])
 def test_plan_cuts_match_oracle(gpu_lib, name, heads, lq, lk, d, b, n):
     """Every cut of the attention call (key ranges, rotated lists) on random
     lists, some of them shorter (one empty), with the partial last block in half
     of them: sampled query blocks against the oracle; the single pass and, with
-    the same lists in a kv_stride that could hold every block (never rotated,
-    planned as a full list), the plain walk, against the same bounds."""
+    the same lists in a kv_stride that could hold every block (planned as a
+    full list, never rotated), against the same bounds."""
     import torch
 
     _say(f"[plan] {name}: H={heads} Lq={lq} Lk={lk} D={d} b={b} n={n}")
@@ -864,7 +870,7 @@ def test_plan_cuts_match_oracle(gpu_lib, name, heads, lq, lk, d, b, n):
     wide[..., :n] = idx
     runs = {"plan": gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, b),
             "one pass": gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, b, split=False),
-            "plain": gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, wide, b)}
+            "wide rows": gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, wide, b)}
     again = gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, b)
     torch.cuda.synchronize()
     assert torch.equal(again[0], runs["plan"][0]) and torch.equal(again[1], runs["plan"][1])
