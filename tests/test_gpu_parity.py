@@ -836,8 +836,8 @@ PLAN_CASES = [
     ("eight-ranges", 1, 128 * 16 + 1, 128 * 64 + 77, 64, 128, 38, 8, False, False),
     ("sixteen-d64-b64", 1, 64 * 144 - 3, 64 * 230 - 7, 64, 64, 115, 16, False, True),
     ("sixteen-d64-b128", 1, 128 * 3 - 3, 128 * 19 - 7, 64, 128, 15, 16, False, False),
-    ("sixteen-d128-b64", 1, 64 * 2 - 3, 64 * 38 - 7, 128, 64, 30, 16, False, False),
-    ("sixteen-d128-b128", 1, 128 * 2 - 3, 128 * 35 - 7, 128, 128, 28, 16, False, False),
+    ("sixteen-d128-b64", 1, 64 * 4 - 3, 64 * 90 - 7, 128, 64, 72, 16, False, False),
+    ("sixteen-d128-b128", 1, 128 * 3 - 3, 128 * 60 - 7, 128, 128, 50, 16, False, False),
     ("rotated-2", 12, 128 * 50 - 3, 128 * 188 - 7, 128, 128, 37, 2, True, False),
     ("rotated-4-d64", 8, 64 * 80 - 3, 64 * 2009 - 7, 64, 64, 100, 4, True, False),
     ("rotated-4-shared", 2, 64 * 196 - 3, 64 * 1027 - 7, 128, 64, 51, 4, True, True),
