@@ -22,11 +22,18 @@ struct AttnPlan {
 // How many XCDs share a (head, range) pair.  One keeps the pair's K/V in one
 // L2, but an XCD with only a few pairs runs as long as its heads' lists are
 // (per-head budgets differ).  So a pair is shared until each XCD has four
-// units, as long as a unit keeps 4,096 query rows (half of what an XCD holds):
-// 8 heads with budgets from 0.5 to 1.5 of the mean, 21,332 queries, took
-// 0.56 ms shared by four and 0.71 unshared; 6,413 queries 0.62 and 0.44.  The
-// units of all pairs have to deal out evenly in any case, but a pair is never
-// shared by more XCDs than it has groups: the work-groups of the empty units
+// units, as long as a unit keeps 3,300 query rows (two fifths of what an XCD
+// holds): 8 heads with budgets from 0.5 to 1.5 of the mean, 21,332 queries, took
+// 0.56 ms shared by four and 0.71 unshared; 6,413 queries 0.62 and 0.44; two
+// heads of such budgets, 26,971 queries, 0.85 ms shared by four and 0.67 by
+// eight (0.61 and 0.72 with equal budgets).  262 shapes timed with every
+// sharing took 3.3% more than with the best one where budgets are equal and 3.8%
+// where they differ; at 4,096 rows 3.2% and 4.9%, shared by eight throughout
+// 6% and 7%.  The units of all pairs have to deal out evenly in any case: up to a
+// sixth of the last round of units empty gains where K/V exceed the L2 (23
+// heads, 3,152 queries, 28,266 keys: 628 us shared by eight, 401 unshared), but
+// costs 5 to 10% where they don't.  A pair is never shared by more XCDs than it
+// has groups: the work-groups of the empty units
 // return at once, yet count as placed when the dispatcher goes round the CUs
 // (dense call, 35 heads of 200 queries, two groups each: 21.5 us shared by
 // eight, 16.4 by one or two), and eight times as many work-groups as items can
@@ -34,7 +41,7 @@ struct AttnPlan {
 inline int attn_spread_bits(int64_t pairs, int64_t groups, int group_rows) {
   auto enough = [&](int bits) {
     const int64_t units = pairs << bits;
-    return units % 8 == 0 && (units >= 32 || ((groups * group_rows) >> (bits + 1)) < 4096);
+    return units % 8 == 0 && (units >= 32 || ((groups * group_rows) >> (bits + 1)) < 3300);
   };
   int bits = 0;
   while (bits < 3 && (int64_t(1) << bits) < groups && !enough(bits)) ++bits;

@@ -86,3 +86,9 @@ def test_few_queries_over_many_keys_take_sixteen_ranges(lib, bh, lq, lk, d, b, s
 def test_short_lists_take_one_range(lib, bh, lq, lk, d, b, stride):
     """Lists of a few blocks: the merge of even two ranges costs more than it saves."""
     assert attn_plan(lib, 1, bh, lq, lk, d, b, stride, True).ranges == 1
+
+
+@pytest.mark.parametrize("bh,lq,bits", [(2, 26_971, 3), (2, 13_000, 2), (8, 6413, 0), (8, 21_332, 2), (24, 72_000, 1)])
+def test_sharing_of_pairs_over_xcds(lib, bh, lq, bits):
+    """One pass at D = 128, b = 64: two long heads, whose lists may differ, go to every XCD."""
+    assert attn_plan(lib, 1, bh, lq, 98_334, 128, 64, 250, False).spread_bits == bits
