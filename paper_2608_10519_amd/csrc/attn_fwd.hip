@@ -23,10 +23,11 @@
 // queries, 144,512 keys and 25% density the call took 33.2 ms rotated and 52.8
 // plain with 4 ranges (8 ranges: 32.8 and 38.1; 16: 34.5 and 36.0; 2: 36.6 and
 // 64.4).  Work-groups that run in step by themselves keep the plain order: the
-// dense call and lists that can name every block (27.8 ms plain, 29.9 rotated,
+// dense call and lists that name every block (27.8 ms plain, 29.9 rotated,
 // at 25,920 queries and 98,432 keys), the first rounds of a call, and one
 // range over the whole sequence, which the window loses (mid scale 5.3 rotated
-// and 4.7 plain).
+// and 4.7 plain).  Each list decides by its own length, so that short lists in
+// rows of full width are rotated too.
 //
 // Per tile of the query block's key-block list, a three-stage pipeline: step t
 // runs the scores of tile t + 1, the softmax of tile t and P V of tile t - 1.
@@ -309,9 +310,10 @@ void attn_fwd_kernel(AttnArgs a) {
       pos_lo = __builtin_amdgcn_readfirstlane(c_lo);
       cnt = __builtin_amdgcn_readfirstlane(c_hi) - pos_lo;
       rot = __builtin_amdgcn_readfirstlane(c_st) - pos_lo;
-      // (out of [0, cnt) only past the range's last entry, or in a list that is
-      // not ascending)
-      if (rot < 0 || rot >= cnt) rot = 0;
+      // A list that names every block is walked from its head (rot is out of
+      // [0, cnt) only past the range's last entry, or in a list that is not
+      // ascending).
+      if (nblk >= a.n_k || rot < 0 || rot >= cnt) rot = 0;
     }
   }
 

@@ -120,10 +120,15 @@ inline double attn_time_us(int64_t bh, int64_t lq, int64_t lk, int d, int block,
 
 // The cut with the least estimated time.  The dense call's work-groups take 64 or
 // 128 rows: 128 feed twice the queries per K/V byte loaded, 64 fill more CUs and
-// pad less.  A sparse call whose rows can name every block takes the ranges of
-// the dense call, so that full lists give the dense call's bits.  With several
-// ranges the lists are rotated (attn_fwd.hip) where the estimate says so and
-// some cannot name every block.
+// pad less.  With several ranges the lists are rotated (attn_fwd.hip) where the
+// estimate says so.  A sparse call whose rows can name every block takes the
+// ranges of the dense call, so that full lists give the dense call's bits; what
+// its lists hold is not known here, and from eight rounds of work-groups on it
+// is rotated (the kernel leaves the lists that are full plain): lists of 25% in
+// rows of full width, 24 heads, 72,000 queries, 144,512 keys, took 50.4 ms in 4
+// plain ranges and take 32.4, as in rows of their own width; 11,520 queries 3.78
+// and 3.17.  Rotated lists do better in narrow ranges (35.5 ms in 2), so of two
+// cuts of full rows that differ by less than 0.6% the one with more ranges is taken.
 inline AttnPlan attn_plan(int64_t bh, int64_t lq, int64_t lk, int d, int block, int64_t kv_stride, bool dense,
                           bool may_split) {
   const int64_t nk = (lk + block - 1) / block;
@@ -139,8 +144,8 @@ inline AttnPlan attn_plan(int64_t bh, int64_t lq, int64_t lk, int d, int block, 
       const bool rounds = bh * r * g * rows > 32768 * attn_waves_per_simd(d);
       for (int rotated = 0; rotated <= (r > 1 && !full && rounds); ++rotated) {
         const double t = attn_time_us(bh, lq, lk, d, block, rho, full, r, rotated, rows);
-        if (plan.group_rows == 0 || t < best) {
-          best = t;
+        if (plan.group_rows == 0 || t < (full && r > plan.ranges ? 1.006 * best : best)) {
+          best = plan.group_rows == 0 ? t : fmin(best, t);
           plan.group_rows = rows;
           plan.ranges = r;
           plan.rotation = rotated ? 32 * 4 * attn_waves_per_simd(d) / (rows / 32) : 0;
@@ -149,6 +154,8 @@ inline AttnPlan attn_plan(int64_t bh, int64_t lq, int64_t lk, int d, int block, 
     }
   if (!dense) plan.group_rows = block;
   const int64_t groups = (lq + plan.group_rows - 1) / plan.group_rows, pairs = bh * plan.ranges;
+  const int64_t held = 32 * 4 * attn_waves_per_simd(d) / (plan.group_rows / 32);  // work-groups an XCD holds
+  if (full && !dense && plan.ranges > 1 && pairs * groups >= 8 * 8 * held) plan.rotation = int(held);
   plan.spread_bits = attn_spread_bits(pairs, groups, plan.group_rows);
   plan.grid = attn_grid(pairs, groups, plan.spread_bits);
   return plan;

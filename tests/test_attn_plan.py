@@ -92,3 +92,13 @@ def test_short_lists_take_one_range(lib, bh, lq, lk, d, b, stride):
 def test_sharing_of_pairs_over_xcds(lib, bh, lq, bits):
     """One pass at D = 128, b = 64: two long heads, whose lists may differ, go to every XCD."""
     assert attn_plan(lib, 1, bh, lq, 98_334, 128, 64, 250, False).spread_bits == bits
+
+
+@pytest.mark.parametrize("lq,lk,rotated", [(72_000, 144_512, True), (11_520, 84_032, True), (640, 84_032, False)])
+def test_rows_of_full_width_are_rotated(lib, lq, lk, rotated):
+    """Lists may be short in rows that could hold every block (one buffer for
+    several budgets): the call is rotated like one with shorter rows."""
+    for stride in (-(-lk // 64), -(-lk // 64) + 9):
+        p = attn_plan(lib, 1, 24, lq, lk, 128, 64, stride, True)
+        assert p.ranges > 1 and (p.rotation > 0) == rotated
+    assert attn_plan(lib, 1, 24, lq, lk, 128, 64, 0, True).rotation == 0  # the dense call is not

@@ -17,7 +17,7 @@ import pytest
 
 import oracle as O
 from synthetic import TINY, Workload, bf16_bits, bf16_to_f64, generate
-from tests.helpers import (keep_for, LSE_ABS, LSE_ABS_SHARP, O_MAX_ABS, O_MAX_ABS_SHARP, bf16_tensor_to_f64, check_gap_rule, check_output,
+from tests.helpers import (attn_plan, keep_for, LSE_ABS, LSE_ABS_SHARP, O_MAX_ABS, O_MAX_ABS_SHARP, bf16_tensor_to_f64, check_gap_rule, check_output,
                            lists_from_device, lists_to_device, to_dev)
 
 pytestmark = pytest.mark.gpu
@@ -885,3 +885,36 @@ def test_plan_cuts_match_oracle(gpu_lib, name, heads, lq, lk, d, b, n):
                 check_output(bf16_tensor_to_f64(o[0, h, t])[None], o_ref[None],
                              lse[0, h, t].cpu().numpy().astype(np.float64)[None], l_ref[None],
                              what=f"{name} {what} head {h} block {i}")
+
+
+def test_full_and_short_lists_in_rows_of_full_width(gpu_lib):
+    """A call with kv_stride = n_k and enough rounds of work-groups to be
+    rotated: lists that name every block give the dense call's bits, the short
+    ones (a fifth of the blocks) beside them match the oracle."""
+    import torch
+
+    heads, lq, lk, d, b = 24, 64 * 90 - 5, 64 * 260 + 9, 128, 64
+    n_q, n_k = -(-lq // b), -(-lk // b)
+    p = attn_plan(gpu_lib, 1, heads, lq, lk, d, b, n_k)
+    assert p.ranges > 1 and p.rotation > 0
+    _say(f"[wide rows] H={heads} Lq={lq} Lk={lk} ranges={p.ranges}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(83)
+    q, k, v = (torch.randn(1, heads, l, d, generator=g, device="cuda").to(torch.bfloat16) for l in (lq, lk, lk))
+    idx = torch.arange(n_k, dtype=torch.int32, device="cuda").repeat(1, heads, n_q, 1)
+    num = torch.full((1, heads, n_q), n_k, dtype=torch.int32, device="cuda")
+    n = n_k // 5
+    short = torch.rand(heads, n_q // 2, n_k, generator=g, device="cuda").topk(n, dim=-1).indices.sort(dim=-1).values
+    idx[0, :, 1::2, :n] = short.to(torch.int32)
+    num[:, :, 1::2] = n
+    o, lse = gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, b)
+    od, ld = gpu_lib.sparstar_dense_attn_fwd(q, k, v, b)
+    torch.cuda.synchronize()
+    full = (torch.arange(lq, device="cuda") // b) % 2 == 0
+    assert torch.equal(o[:, :, full], od[:, :, full]) and torch.equal(lse[:, :, full], ld[:, :, full])
+    for h, i in [(0, 1), (7, 45), (23, 89)]:
+        t = slice(i * b, min((i + 1) * b, lq))
+        o_ref, l_ref = O.sparse_attention(bf16_tensor_to_f64(q[0, h, t]), bf16_tensor_to_f64(k[0, h]),
+                                          bf16_tensor_to_f64(v[0, h]), [idx[0, h, i, :n].tolist()], b)
+        check_output(bf16_tensor_to_f64(o[0, h, t])[None], o_ref[None], lse[0, h, t].cpu().numpy().astype(np.float64)[None],
+                     l_ref[None], what=f"short list, head {h} block {i}")
