@@ -235,13 +235,24 @@ void attn_fwd_kernel(AttnArgs a) {
   // each time, so that every XCD gets every range in turn: forced blocks make
   // some ranges several times as long as others (reference and text forced at
   // 720p: 79 ms turned, 122 unturned).  An XCD runs a unit's groups one after the
-  // other.  (All of it fits 32 bits, as the grid does.)
+  // other.  With all eight XCDs on a pair the items simply go in order, which
+  // leaves no empty work-groups.  (All of it fits 32 bits, as the grid does.)
   const uint32_t n_g = DENSE ? (uint32_t)((a.lq + 32 * NW - 1) / (32 * NW)) : (uint32_t)a.n_q;  // groups per head
   const uint32_t range_bits = SPLIT ? __builtin_ctz(a.n_splits) : 0;  // n_splits is a power of two
-  const uint32_t n_u = (n_g + (1u << a.spread_bits) - 1) >> a.spread_bits;
-  const uint32_t id = blockIdx.x / 8, ui = id / n_u, gi = id - ui * n_u;
-  const uint32_t unit = ui * 8 + (blockIdx.x + ui) % 8, pair = unit >> a.spread_bits;
-  const int qg = (int)((gi << a.spread_bits) + (unit & ((1u << a.spread_bits) - 1)));
+  uint32_t gi, pair;  // gi: the place of the group among the pair's on this XCD
+  int qg;
+  if (a.spread_bits == 3) {
+    pair = blockIdx.x / n_g;
+    qg = (int)(blockIdx.x - pair * n_g);
+    gi = (uint32_t)qg >> 3;
+  } else {
+    const uint32_t n_u = (n_g + (1u << a.spread_bits) - 1) >> a.spread_bits;
+    const uint32_t id = blockIdx.x / 8, ui = id / n_u;
+    gi = id - ui * n_u;
+    const uint32_t unit = ui * 8 + (blockIdx.x + ui) % 8;
+    pair = unit >> a.spread_bits;
+    qg = (int)((gi << a.spread_bits) + (unit & ((1u << a.spread_bits) - 1)));
+  }
   if (pair >= ((uint32_t)a.bh << range_bits) || qg >= (int)n_g) return;  // uniform: past the last unit or group
   const int64_t bh = pair >> range_bits;
   const int split = (int)(pair & ((1u << range_bits) - 1));

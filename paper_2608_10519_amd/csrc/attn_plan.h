@@ -32,27 +32,29 @@ struct AttnPlan {
 // 6% and 7%.  The units of all pairs have to deal out evenly in any case: up to a
 // sixth of the last round of units empty gains where K/V exceed the L2 (23
 // heads, 3,152 queries, 28,266 keys: 628 us shared by eight, 401 unshared), but
-// costs 5 to 10% where they don't.  A pair is never shared by more XCDs than it
-// has groups: the work-groups of the empty units
-// return at once, yet count as placed when the dispatcher goes round the CUs
-// (dense call, 35 heads of 200 queries, two groups each: 21.5 us shared by
-// eight, 16.4 by one or two), and eight times as many work-groups as items can
-// pass the launch limit of 2^32 threads.
+// costs 5 to 10% where they don't.
+//
+// Sharing by two or four leaves empty work-groups at the end of the units.  They
+// return at once, yet count as placed when the dispatcher goes round the CUs, so
+// where they would be more than a sixteenth of the items the pairs are shared by
+// eight, which needs none.  19 heads of 13 groups, about one work-group per CU:
+// 71.1 us with a fifth of the work-groups empty, 56.2 without; 25 heads of 9 30.8 and
+// 21.8.
 inline int attn_spread_bits(int64_t pairs, int64_t groups, int group_rows) {
   auto enough = [&](int bits) {
-    const int64_t units = pairs << bits;
-    return units % 8 == 0 && (units >= 32 || ((groups * group_rows) >> (bits + 1)) < 3300);
+    const int64_t units = pairs << bits, empty = units * ((groups + (1 << bits) - 1) >> bits) - pairs * groups;
+    return units % 8 == 0 && 16 * empty <= pairs * groups &&
+           (units >= 32 || ((groups * group_rows) >> (bits + 1)) < 3300);
   };
   int bits = 0;
-  while (bits < 3 && (int64_t(1) << bits) < groups && !enough(bits)) ++bits;
+  while (bits < 3 && !enough(bits)) ++bits;
   return bits;
 }
 
-// Work-groups launched: whole rounds of eight units (one per XCD), each of the
-// groups a unit can hold.  The kernel's decode of blockIdx matches.
+// Work-groups launched: every item, or the groups that whole units can hold.
+// The kernel's decode of blockIdx matches.
 inline int64_t attn_grid(int64_t pairs, int64_t groups, int bits) {
-  const int64_t units = ((pairs << bits) + 7) / 8 * 8;
-  return units * ((groups + (1 << bits) - 1) >> bits);
+  return bits == 3 ? pairs * groups : (pairs << bits) * ((groups + (1 << bits) - 1) >> bits);
 }
 
 // An estimate of a call's time in microseconds, for one cut of it.  rho is the
@@ -92,7 +94,8 @@ inline double attn_time_us(int64_t bh, int64_t lq, int64_t lk, int d, int block,
   const int bits = attn_spread_bits(pairs, groups, group_rows);
   const double units = double(((pairs << bits) + 7) / 8);                    // per XCD
   const double unit_groups = double((groups + (1 << bits) - 1) >> bits);
-  const double work_groups = units * unit_groups, rounds = work_groups / held;
+  const double work_groups = bits == 3 ? double((pairs * groups + 7) / 8) : units * unit_groups;
+  const double rounds = work_groups / held;
   const double whole = floor(rounds), part = rounds - whole;
 
   const int sub = block / 32;
