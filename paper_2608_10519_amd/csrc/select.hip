@@ -288,10 +288,16 @@ __device__ __forceinline__ SelRule rule_sampled(const uint32_t (&key)[C], int kk
 // case) a block is taken when forced or above thr: key - 1 >= thr as unsigned,
 // which holds for the forced key 0 and not for a block past n_k (thr is at least
 // the least real key less one).  The stores go through a buffer descriptor, the
-// lanes that take nothing past its end, so that the loop has no branch.
-template <int C>
-__device__ __forceinline__ void emit_row(const uint32_t (&key)[C], SelRule rule, int lane, int32_t* out, int cap,
-                                         int32_t* num_out) {
+// lanes that take nothing past its end, so that the loop has no branch.  (`out` must
+// be the same for the whole wave by construction, from a scalar wave index: a
+// descriptor in vector registers costs a loop around every store: 385 us for the
+// fused kernel at 27,000 rows of 2,259 blocks, 365 without.)  With SHORT, for
+// the instance that also holds rows of a few blocks, the chunks past n_k are left
+// out (fused, 18 blocks: 6.5 us, 6.8 with them); longer rows only lose by the
+// branches (365 us, 368 with them).
+template <int C, bool SHORT>
+__device__ __forceinline__ void emit_row(const uint32_t (&key)[C], SelRule rule, int lane, int n_k, int32_t* out,
+                                         int cap, int32_t* num_out) {
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(out, (short)0, cap * 4, 0x00020000);
   int pos = 0;
   auto put = [&](bool take, int c) {
@@ -302,11 +308,13 @@ __device__ __forceinline__ void emit_row(const uint32_t (&key)[C], SelRule rule,
   };
   if (rule.take_ties == 0) {
 #pragma unroll
-    for (int c = 0; c < C; ++c) put(key[c] - 1u >= rule.thr, c);
+    for (int c = 0; c < C; ++c)
+      if (!SHORT || 64 * c < n_k) put(key[c] - 1u >= rule.thr, c);
   } else {
     uint32_t ties = 0;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
+      if (SHORT && 64 * c >= n_k) continue;
       const bool tie = key[c] == rule.thr;  // thr >= kLeastKey: never a forced block
       const uint64_t tie_mask = __ballot(tie);
       const uint32_t tie_rank = ties + (uint32_t)lanes_below(tie_mask);
@@ -382,8 +390,8 @@ __global__ __launch_bounds__(64 * kSelWaves) void select_reg_kernel(SelectArgs a
       rule = rule_full<C>(key, kk);
     }
   }
-  emit_row<C>(key, rule, lane, a.kv_indices + row * a.stride, a.stride < a.n_k ? a.stride : a.n_k,
-              a.kv_num_blocks + row);
+  emit_row<C, false>(key, rule, lane, a.n_k, a.kv_indices + row * a.stride, a.stride < a.n_k ? a.stride : a.n_k,
+                     a.kv_num_blocks + row);
 }
 
 // ---------------------------------------------------------------------------
@@ -404,7 +412,7 @@ __global__ __launch_bounds__(64 * kSelWaves) void select_reg_kernel(SelectArgs a
 template <int D, int C>
 __global__ __launch_bounds__(64 * kFusedRows) void score_select_kernel(ScoreSelectArgs a) {
   extern __shared__ uint32_t fused_keys[];  // [kFusedRows][row_len] order keys
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
   const int groups = (a.n_q + kFusedRows - 1) / kFusedRows;
   const int64_t wl = xcd_linear(blockIdx.x, (int64_t)gridDim.x);
   const int64_t bh = wl / groups;
@@ -496,7 +504,8 @@ __global__ __launch_bounds__(64 * kFusedRows) void score_select_kernel(ScoreSele
   // the row's own LDS keys are in registers now: their space holds the
   // bracketed candidates (at most min(n_k, 64 kSelCand) of them)
   const SelRule rule = kk > 0 ? rule_sampled<C, false>(key, kk, a.n_sel, samp, rk, lane) : SelRule{0xffffffffu, 0u};
-  emit_row<C>(key, rule, lane, a.kv_indices + r * a.stride, a.stride < a.n_k ? a.stride : a.n_k, a.kv_num_blocks + r);
+  emit_row<C, (C <= 8)>(key, rule, lane, a.n_k, a.kv_indices + r * a.stride, a.stride < a.n_k ? a.stride : a.n_k,
+                        a.kv_num_blocks + r);
 }
 
 size_t score_select_lds_bytes(int n_k) { return (size_t)kFusedRows * ((n_k + 15) / 16 * 16) * sizeof(uint32_t); }
