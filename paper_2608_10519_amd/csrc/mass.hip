@@ -97,7 +97,6 @@ __device__ __forceinline__ uint32_t order_key(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-constexpr int kTopkThreads = 1024;
 constexpr int kTopkSamples = 512;
 constexpr int kTopkCand = 32768;  // candidate keys held in LDS (128 KB)
 
@@ -136,19 +135,29 @@ __device__ __forceinline__ void find_digit(const uint32_t* hist, uint32_t above,
 // inside it (a sixth of the row or so) in LDS, where a radix select finds the
 // n-th largest; a second pass, in the row's order, sums exp(s - lse) over the
 // keys above it.  A row of up to 32,768 keys goes to LDS as it is.  If the
-// bracket missed or overflows (many equal logits), the radix select runs from
-// memory.
+// bracket missed or overflows, the radix select runs from memory: with many equal
+// logits, and in long rows, since the bracket holds about 16% of the row where a
+// quarter of it is wanted and 18% where half is, which pass 32,768 keys at some
+// 205,000 and 178,000 keys (24 heads, 8 rows, a quarter wanted: 292 us in all
+// at 144,512 keys, 735 at 205,000; histograms over the whole row 1,705).
 // Bound by one CU's work per row (192 rows for 256 CUs, 144,512 keys each): two
 // passes of key forming, compaction and expf, and the LDS steps between them:
 // 110 us (loads in flight do not matter, 8 or 24 per lane); radix select in four passes of LDS
 // histograms over the row, 256 threads a row, 965 us.
-__global__ __launch_bounds__(kTopkThreads) void topk_mass_kernel(TopkArgs a) {
-  __shared__ uint32_t cand[kTopkCand];
-  __shared__ uint32_t samp[kTopkSamples], rank[kTopkSamples], hist[256];
+//
+// Short rows take instances with room for just the row, so that a CU holds eight
+// (2,048 keys) or four (8,192): the large instance fills a CU's LDS.  All of them
+// add a whole row up in the same order.
+template <int CAND, int NT>
+__global__ __launch_bounds__(NT) void topk_mass_kernel(TopkArgs a) {
+  constexpr bool WHOLE = CAND < kTopkCand;  // for rows of up to CAND keys only
+  constexpr int SAMP = WHOLE ? 1 : kTopkSamples;
+  __shared__ uint32_t cand[CAND];
+  __shared__ uint32_t samp[SAMP], rank[SAMP], hist[256];
   __shared__ uint32_t sel[2];        // chosen digit, count of keys above it
   __shared__ uint32_t bracket[2];    // the lower and the upper key
   __shared__ uint32_t n_above, n_cand;
-  __shared__ float part[kTopkThreads];
+  __shared__ float part[NT];
   const int64_t row = blockIdx.x;  // bh * n_rows + r
   const int64_t bh = row / a.n_rows;
   const int r = (int)(row % a.n_rows);
@@ -164,7 +173,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_mass_kernel(TopkArgs a) {
   }
   // ---- the bracket [lo, hi) of keys (hi = 0: no upper end)
   uint32_t lo = 0, hi = 0;
-  const bool whole = lk <= (uint32_t)kTopkCand;  // the row as it is
+  const bool whole = WHOLE || lk <= (uint32_t)CAND;  // the row as it is
   if (!whole) {
     if (tid < kTopkSamples) {
       samp[tid] = order_key(s[((2 * (uint64_t)tid + 1) * lk) / (2 * kTopkSamples)]);
@@ -175,7 +184,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_mass_kernel(TopkArgs a) {
     {
       // samples larger than sample i (equal ones in index order), half of the
       // samples per thread
-      constexpr int kShare = kTopkSamples * kTopkSamples / kTopkThreads;  // samples per thread
+      constexpr int kShare = kTopkSamples * kTopkSamples / NT;  // samples per thread
       const int i = tid % kTopkSamples, q0 = tid / kTopkSamples * kShare;
       const uint32_t own = samp[i];
       uint32_t n = 0;
@@ -206,18 +215,18 @@ __global__ __launch_bounds__(kTopkThreads) void topk_mass_kernel(TopkArgs a) {
   // ---- one pass over the row
   constexpr int U = 16;
   uint32_t above_t = 0;
-  for (uint32_t base = 0; base < lk; base += U * kTopkThreads) {
+  for (uint32_t base = 0; base < lk; base += U * NT) {
     uint32_t key[U], n_in = 0;
     uint64_t mask[U];
     float x[U];
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      const uint32_t u = base + k * kTopkThreads + tid;
+      const uint32_t u = base + k * NT + tid;
       x[k] = s[u < lk ? u : lk - 1];
     }
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-      const uint32_t u = base + k * kTopkThreads + tid;
+      const uint32_t u = base + k * NT + tid;
       key[k] = order_key(x[k]);
       if (whole && u < lk) cand[u] = key[k];
       const bool up = u < lk && hi != 0 && key[k] >= hi;
@@ -234,7 +243,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_mass_kernel(TopkArgs a) {
     for (int k = 0; k < U; ++k) {
       const uint32_t pos = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask[k] >> 32),
                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)mask[k], 0u));
-      if (((mask[k] >> lane) & 1ull) && pos < (uint32_t)kTopkCand) cand[pos] = key[k];
+      if (((mask[k] >> lane) & 1ull) && pos < (uint32_t)CAND) cand[pos] = key[k];
       at += (uint32_t)__popcll(mask[k]);
     }
   }
@@ -243,7 +252,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_mass_kernel(TopkArgs a) {
   if (lane == 0) atomicAdd(&n_above, above_t);
   __syncthreads();
   const uint32_t g_hi = n_above, m = whole ? lk : n_cand;
-  const bool in_lds = g_hi < want && want <= g_hi + m && m <= (uint32_t)kTopkCand;  // uniform
+  const bool in_lds = g_hi < want && want <= g_hi + m && m <= (uint32_t)CAND;  // uniform
 
   // ---- radix select of the want-th largest key, most significant digit first,
   // among the candidates or, where the bracket failed, over the whole row
@@ -253,7 +262,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_mass_kernel(TopkArgs a) {
   for (int shift = 24; shift >= 0; shift -= 8) {
     if (tid < 256) hist[tid] = 0;
     __syncthreads();
-    for (uint32_t u = tid; u < n_keys; u += kTopkThreads) {
+    for (uint32_t u = tid; u < n_keys; u += NT) {
       const uint32_t key = in_lds ? cand[u] : order_key(s[u]);
       const bool in = (key & pmask) == prefix;
       const uint32_t d = (key >> shift) & 255u;
@@ -280,23 +289,23 @@ __global__ __launch_bounds__(kTopkThreads) void topk_mass_kernel(TopkArgs a) {
   // runs in the row's order whatever the candidates' order in LDS: the call is
   // deterministic.
   auto value = [](uint32_t k) { return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k); };
-  const int n_acc = whole ? 256 : kTopkThreads;
+  const int n_acc = whole ? 256 : NT;
   float sum = 0.f;
   if (whole) {
     if (tid < n_acc)
       for (uint32_t u = tid; u < lk; u += n_acc)
         if (cand[u] > prefix) sum += expf(value(cand[u]) - lse);
   } else {
-    for (uint32_t base = 0; base < lk; base += U * kTopkThreads) {
+    for (uint32_t base = 0; base < lk; base += U * NT) {
       float x[U];
 #pragma unroll
       for (int k = 0; k < U; ++k) {
-        const uint32_t u = base + k * kTopkThreads + tid;
+        const uint32_t u = base + k * NT + tid;
         x[k] = s[u < lk ? u : lk - 1];
       }
 #pragma unroll
       for (int k = 0; k < U; ++k)
-        if (base + k * kTopkThreads + tid < lk && order_key(x[k]) > prefix) sum += expf(x[k] - lse);
+        if (base + k * NT + tid < lk && order_key(x[k]) > prefix) sum += expf(x[k] - lse);
     }
   }
   part[tid] = sum;
@@ -326,7 +335,13 @@ hipError_t launch_topk_mass(const TopkArgs& a, int d, hipStream_t stream) {
   else return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  topk_mass_kernel<<<(unsigned)(a.bh * a.n_rows), kTopkThreads, 0, stream>>>(a);
+  // 6,144 rows of 1,152 keys: 52 us for the call, 250 with the large instance
+  // alone; 3,072 of 8,192 keys: 134 and 274.  With fewer rows than CUs the number
+  // held by one does not matter, and more threads a row do (192 rows of 8,192).
+  const unsigned rows = (unsigned)(a.bh * a.n_rows);
+  if (a.lk <= 2048) topk_mass_kernel<2048, 256><<<rows, 256, 0, stream>>>(a);
+  else if (a.lk <= 8192 && rows > 256) topk_mass_kernel<8192, 512><<<rows, 512, 0, stream>>>(a);
+  else topk_mass_kernel<kTopkCand, 1024><<<rows, 1024, 0, stream>>>(a);
   return hipGetLastError();
 }
 

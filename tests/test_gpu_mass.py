@@ -167,6 +167,26 @@ def test_token_topk_mass_d128_ragged(gpu_lib, sharp):
     _topk_case(gpu_lib, q, k, rows, n_tok, scale)
 
 
+@pytest.mark.parametrize("lk,H,n_rows,distinct", [(1, 2, 3, 0), (255, 3, 16, 0), (2047, 2, 5, 0), (2048, 17, 16, 0),
+                                                  (2049, 17, 16, 0), (2049, 2, 5, 3), (8192, 17, 16, 0), (8193, 17, 16, 0),
+                                                  (8191, 16, 16, 0), (2048, 17, 16, 1)])
+def test_token_topk_mass_short_rows(gpu_lib, lk, H, n_rows, distinct):
+    """Row lengths around 2,048 and 8,192 keys, with up to 256 rows and more:
+    the limits between the instances that search a row whole."""
+    _say(f"[mass] token top-n short rows Lk={lk} {H} x {n_rows} rows distinct={distinct}")
+    rng = np.random.default_rng(lk + H)
+    Lq, d = 16, 64
+    from synthetic.workloads import bf16_bits
+
+    q = bf16_bits(rng.standard_normal((1, H, Lq, d)).astype(np.float32))
+    k = rng.standard_normal((1, H, distinct or lk, d)).astype(np.float32)
+    if distinct:
+        k = k[:, :, np.arange(lk) % distinct]
+    picks = [1, 2, lk // 100, lk // 10, lk // 4, lk // 2, lk - 1, lk, 0, lk + 9, lk // 3]
+    n_tok = [[picks[(7 * h + r) % len(picks)] for r in range(n_rows)] for h in range(H)]
+    _topk_case(gpu_lib, q, bf16_bits(k), list(range(n_rows)), n_tok)
+
+
 @pytest.mark.parametrize("lk,d,n_rows,distinct", [(32_768, 64, 16, 0), (32_769, 128, 3, 0), (40_001, 128, 16, 0),
                                                   (70_003, 64, 1, 0), (40_004, 64, 4, 7), (33_000, 128, 2, 1)])
 def test_token_topk_mass_long_rows(gpu_lib, lk, d, n_rows, distinct):

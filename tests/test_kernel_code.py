@@ -9,24 +9,35 @@ import pytest
 from paper_2608_10519_amd import build as B
 
 
-@pytest.fixture(scope="module")
-def select_asm(tmp_path_factory):
+def _compile(tmp_path, source):
     if not os.path.exists(B.HIPCC):
         pytest.skip("hipcc is not available")
-    out = str(tmp_path_factory.mktemp("asm") / "select.s")
+    out = str(tmp_path / "kernels.asm")
     r = subprocess.run([B.HIPCC, *B.FLAGS, "-x", "hip", "--cuda-device-only", "-S",
-                        os.path.join(B.CSRC, "select.hip"), "-o", out], capture_output=True, text=True)
+                        os.path.join(B.CSRC, source), "-o", out], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
-    text = open(out).read()
-    return {m.group(1): m.group(2) for m in re.finditer(r"^(_ZN8sparstar\w+):.*?\n(.*?)s_endpgm", text, re.S | re.M)}
+    return open(out).read()
 
 
-def test_list_stores_take_a_scalar_descriptor(select_asm):
+def test_list_stores_take_a_scalar_descriptor(tmp_path):
     """The selectors store the list through a buffer descriptor.  Kept in vector
     registers it is read back lane by lane around every store: then there are
     several v_readfirstlane per store instead of a few per kernel."""
-    kernels = {n: t for n, t in select_asm.items() if "score_select_kernel" in n or "select_reg_kernel" in n}
+    text = _compile(tmp_path, "select.hip")
+    bodies = {m.group(1): m.group(2) for m in re.finditer(r"^(_ZN8sparstar\w+):.*?\n(.*?)s_endpgm", text, re.S | re.M)}
+    kernels = {n: t for n, t in bodies.items() if "score_select_kernel" in n or "select_reg_kernel" in n}
     assert len(kernels) == 8 + 7, sorted(kernels)  # fused: two head dims, four row lengths
     for name, text in kernels.items():
         stores, reads = text.count("buffer_store_dword"), text.count("v_readfirstlane_b32")
         assert stores > 0 and reads <= 16 + stores // 8, (name, stores, reads)
+
+
+def test_short_rows_of_the_mass_kernel_share_a_cu(tmp_path):
+    """The ranking kernel has instances that fit a CU (160 KB of LDS, 2,048
+    threads) eight and four times, for calls with many short rows."""
+    text = _compile(tmp_path, "mass.hip")
+    fits = []
+    for m in re.finditer(r"\.group_segment_fixed_size: (\d+)(?:(?!group_segment).)*?\.max_flat_workgroup_size: (\d+)"
+                         r"\s+\.name:\s+(\S*topk_mass_kernel\S*)", text, re.S):
+        fits.append(min(160 * 1024 // int(m.group(1)), 2048 // int(m.group(2))))
+    assert sorted(fits) == [1, 4, 8]
