@@ -13,7 +13,7 @@ import numpy as np
 import pytest
 
 from synthetic import TINY, generate
-from tests.helpers import keep_for, to_dev
+from tests.helpers import attn_plan, keep_for, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -29,7 +29,8 @@ def test_graph_replay_matches_eager(gpu_lib, split, fused):
     import torch
 
     S = gpu_lib
-    w = TINY.with_(name="graph", head_dim=128, lq=64 * 40 + 9, l_ref=64 * 30 + 3, l_text=150, heads=3, seed=31)
+    w = TINY.with_(name="graph", head_dim=128, lq=64 * 40 + 9, l_ref=64 * 30 + 3, l_text=150, heads=3, seed=31,
+                   density=0.5)
     _say(f"[graph] H={w.heads} D={w.head_dim} Lq={w.lq} Lk={w.lk} split={split} fused={fused}")
     qb, kb, vb = generate(w)
     q, k, v = to_dev(qb), to_dev(kb), to_dev(vb)
@@ -38,6 +39,7 @@ def test_graph_replay_matches_eager(gpu_lib, split, fused):
     Lk = k.shape[2]
     n_q = -(-Lq // w.block)
     stride = S.sparstar_kv_stride(H, Lk, w.block, w.density, keep)
+    assert (attn_plan(S, B, H, Lq, Lk, D, w.block, stride, split).ranges > 1) == split
     num = torch.empty((B, H, n_q), dtype=torch.int32, device="cuda")
     idx = torch.empty((B, H, n_q, stride), dtype=torch.int32, device="cuda")
     ws = torch.empty(S.sparstar_score_workspace_bytes(B, H, Lq, Lk, D, w.block), dtype=torch.uint8, device="cuda")

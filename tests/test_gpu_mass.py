@@ -10,8 +10,9 @@ Tolerances
   - sparstar_token_topk_mass with the exact (oracle) lse: each logit is an fp32
     dot product of bf16 inputs (exact products, D rounded additions: error at
     most D u s sum_d |q_d k_d|, u = 2^-24), then one subtraction of the fp32
-    lse (2 u (1 + |lse|)); the weights are summed in fp32 per lane over Lk/256
-    terms and then over a 256-wide tree ((Lk/256 + 8) u relative).  A swap of
+    lse (2 u (1 + |lse|)); the weights are summed in fp32 per lane and then over
+    the lanes in a tree: Lk/256 terms and 256 lanes for rows of up to 32,768 keys
+    ((Lk/256 + 8) u relative), Lk/1024 and 1,024 beyond ((Lk/1024 + 10) u).  A swap of
     two logits closer than the logit error at the n-th place stays inside the
     same bound.
   - with the dense kernel's lse: a relative exp(LSE_ABS) - 1 on top of that.
@@ -39,7 +40,8 @@ def _topk_tol(qr, kh, scale, lse_rows, ref):
     d = qr.shape[1]
     s = scale if scale else 1.0 / math.sqrt(d)
     logit = 1.01 * d * U32 * s * (np.abs(qr) @ np.abs(kh).T).max(axis=1) + 2 * U32 * (1 + np.abs(lse_rows))
-    summ = (kh.shape[0] / 256 + 8) * U32
+    lk = kh.shape[0]
+    summ = ((lk / 256 + 8) if lk <= 32_768 else (lk / 1024 + 10)) * U32
     return ref * (np.expm1(logit) + summ + 4 * U32) + 1e-7
 
 

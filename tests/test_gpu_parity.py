@@ -211,10 +211,11 @@ def test_batch_of_two_end_to_end(gpu_lib, split):
     qb_, kb_, vb_ = generate(w)
     q, k, v = to_dev(qb_), to_dev(kb_), to_dev(vb_)
     keep, keep_ref = keep_for(gpu_lib, w)
-    budgets = [0.2, 0.3, 0.45]
+    budgets = [0.2, 0.45, 0.8]
     n_q = -(-w.lq // w.block)
     num, idx = gpu_lib.sparstar_score_blocks(q, k, w.block, budgets, keep)
     nf, xf = gpu_lib.sparstar_score_blocks(q, k, w.block, budgets, keep, fused=True)
+    _assert_splits(gpu_lib, w, split, idx.shape[-1])
     o, lse = gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, w.block, split=split)
     torch.cuda.synchronize()
     lists, lists_f = lists_from_device(num, idx), lists_from_device(nf, xf)
@@ -387,8 +388,8 @@ def _attn_case(gpu_lib, w: Workload, lists_h, scale=None, v_override=None, q_ove
     if k_override is not None:
         kb_ = k_override(kb_)
     n_q = -(-w.lq // w.block)
-    _assert_splits(gpu_lib, w, split)
     num, idx = lists_to_device([lists_h], n_q, stride)
+    _assert_splits(gpu_lib, w, split, idx.shape[-1])
     q, k, v = to_dev(qb_), to_dev(kb_), to_dev(vb_)
     o, lse = gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, w.block, softmax_scale=scale or 0.0, split=split)
     torch.cuda.synchronize()
@@ -400,11 +401,10 @@ def _attn_case(gpu_lib, w: Workload, lists_h, scale=None, v_override=None, q_ove
     return og, lg, o_ref, l_ref, (qb_, kb_, vb_)
 
 
-# Every case has at least 16 key blocks (the most key ranges the split path
-# takes) and a partial last key block, so the split runs for each of the four
-# (D, b) instances; _attn_case asserts that it does.  Their lists are short, so
-# they take 8 ranges; test_sixteen_key_ranges_match_oracle widens kv_stride to
-# reach the 16-range launch on the same inputs.
+# Every case has at least 16 key blocks (fewer are never split) and a partial
+# last key block, and lists long enough that the split runs for each of the four
+# (D, b) instances; _attn_case asserts that it does.  PLAN_CASES below has every
+# number of key ranges.
 ATTN_CASES = [
     ("tiny", TINY),
     ("d128-b64-ragged", TINY.with_(name="a1", head_dim=128, lq=500, l_ref=600, l_text=77, heads=3, seed=17)),
@@ -414,11 +414,11 @@ ATTN_CASES = [
 ]
 
 
-def _assert_splits(lib, w: Workload, split: bool):
-    """The split path only runs when the library asks for a workspace."""
-    if split:
-        n = lib.sparstar_attn_workspace_bytes(w.batch, w.heads, w.lq, w.lk, w.head_dim, w.block)
-        assert n > 0, f"{w.name}: split requested but the library asks for no workspace"
+def _assert_splits(lib, w: Workload, split: bool, kv_stride: int = 0):
+    """With a workspace the library plans several key ranges for this call
+    (kv_stride 0: the dense call), without one a single pass."""
+    p = attn_plan(lib, w.batch, w.heads, w.lq, w.lk, w.head_dim, w.block, kv_stride, split)
+    assert (p.ranges > 1) == split, f"{w.name}: {p.ranges} key ranges planned, split={split}"
 
 
 def _random_lists(w: Workload, rng, heads=None):
@@ -450,23 +450,19 @@ def test_sparse_attention_matches_oracle(gpu_lib, name, w, sharp, split):
     _say(f"[attn] {name}: max |dO| = {err:.2e}")
 
 
-# Lists that can hold this many keys (kv_stride x block size) or more take 16
-# key ranges on the split path, shorter ones 8 (include/sparstar.h).
-SIXTEEN_RANGES_FROM_KEYS = 24576
-
-
 @pytest.mark.parametrize("name,w", ATTN_CASES, ids=[c[0] for c in ATTN_CASES])
-def test_sixteen_key_ranges_match_oracle(gpu_lib, name, w):
-    """The same lists padded to a kv_stride of 24,576 keys take the 16-range
-    split launch; they must meet the oracle as the 8-range launch does."""
+def test_lists_in_wider_rows_match_oracle(gpu_lib, name, w):
+    """The same lists in rows that could hold every block and more (kv_stride
+    past n_k): the call is cut like one with full lists, and the entries past a
+    list's count are not read as part of it."""
     rng = np.random.default_rng(zlib.crc32(name.encode()) % 1000 + 11)
     lists_h = _random_lists(w, rng)
-    stride = -(-SIXTEEN_RANGES_FROM_KEYS // w.block)
-    _say(f"[attn] 16 ranges {name}: kv_stride={stride}")
-    og, lg, o_ref, l_ref, _ = _attn_case(gpu_lib, w, lists_h, stride=stride)
+    n_k = -(-w.lk // w.block)
+    _say(f"[attn] wide rows {name}: {n_k} key blocks, kv_stride={n_k + 37}")
+    og, lg, o_ref, l_ref, _ = _attn_case(gpu_lib, w, lists_h, stride=n_k + 37)
     check_output(og, o_ref, lg, l_ref, what=name)
-    og8, lg8, _, _, _ = _attn_case(gpu_lib, w, lists_h, stride=stride - 1)
-    check_output(og8, o_ref, lg8, l_ref, what=name + " (8 ranges)")
+    full = attn_plan(gpu_lib, 1, w.heads, w.lq, w.lk, w.head_dim, w.block, n_k + 37)
+    assert full.ranges == attn_plan(gpu_lib, 1, w.heads, w.lq, w.lk, w.head_dim, w.block, 0).ranges
 
 
 @pytest.mark.parametrize("name,w", ATTN_CASES, ids=[c[0] for c in ATTN_CASES])
@@ -526,17 +522,40 @@ def test_dense_attention_matches_oracle(gpu_lib, name, w, split):
                  np.stack([r[1] for r in refs])[None], what=name)
 
 
+@pytest.mark.parametrize("heads,lq,lk,d,ranges,split", [
+    (17, 64 * 21 - 9, 64 * 14 + 5, 64, 1, False), (17, 64 * 21 - 9, 64 * 14 + 5, 128, 1, False),
+    (2, 64 * 9 - 5, 64 * 40 + 9, 64, 16, True), (5, 64 * 9 - 5, 64 * 40 + 9, 128, 8, True),
+    (5, 64 * 21 - 9, 64 * 40 + 9, 128, 4, True)])
+def test_dense_groups_of_two_blocks_match_oracle(gpu_lib, heads, lq, lk, d, ranges, split):
+    """The dense call's 128-row work-groups at b = 64, single pass and split, over
+    an odd number of query blocks (the last work-group is half empty)."""
+    import torch
+
+    p = attn_plan(gpu_lib, 1, heads, lq, lk, d, 64, 0, split)
+    assert (p.group_rows, p.ranges) == (128, ranges) and -(-lq // 64) % 2 == 1
+    _say(f"[dense] 128-row groups H={heads} Lq={lq} Lk={lk} D={d} ranges={ranges}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(97)
+    q, k, v = (torch.randn(1, heads, l, d, generator=g, device="cuda").to(torch.bfloat16) for l in (lq, lk, lk))
+    o, lse = gpu_lib.sparstar_dense_attn_fwd(q, k, v, 64, split=split)
+    torch.cuda.synchronize()
+    for h in (0, heads - 1):
+        o_ref, l_ref = O.dense_attention(*(bf16_tensor_to_f64(x[0, h]) for x in (q, k, v)))
+        check_output(bf16_tensor_to_f64(o[0, h])[None], o_ref[None], lse[0, h].cpu().numpy().astype(np.float64)[None],
+                     l_ref[None], what=f"head {h}")
+
+
 @pytest.mark.parametrize("split,long", [(True, False), (True, True), (False, False)],
                          ids=["split", "split-16-ranges", "onepass"])
 def test_full_lists_equal_dense(gpu_lib, split, long):
     """rho = 1 (every block listed) equals the dense forward, bit for bit; the
-    long case has 24,576 keys and more, so both calls take 16 key ranges."""
+    long case has few queries over 24,616 keys, so both calls take 16 key ranges."""
     import torch
 
     w = ATTN_CASES[1][1]
     if long:
-        w = w.with_(name="a1-long", heads=1, lq=300, l_ref=SIXTEEN_RANGES_FROM_KEYS + 40 - w.l_text - 300)
-        assert w.lk == SIXTEEN_RANGES_FROM_KEYS + 40
+        w = w.with_(name="a1-long", heads=1, lq=300, l_ref=24_616 - w.l_text - 300)
+        assert attn_plan(gpu_lib, 1, w.heads, w.lq, w.lk, w.head_dim, w.block).ranges == 16
     _say(f"[dense==sparse(all)] split={split} Lk={w.lk}")
     _assert_splits(gpu_lib, w, split)
     qb_, kb_, vb_ = generate(w)
@@ -574,41 +593,51 @@ def test_zero_queries_average_selected_values(gpu_lib):
     assert n_k > 1
 
 
-@pytest.mark.parametrize("split", [True, False], ids=["split", "onepass"])
-def test_empty_and_invalid_list_entries(gpu_lib, split):
+# (name, heads, Lq, Lk, D, b, listed blocks, split): the single pass, plain key
+# ranges, and rotated ones, where the start of the walk depends on the entries
+INVALID_LIST_CASES = [
+    ("onepass", 2, 512, 64 * 18, 64, 64, 4, False),
+    ("split", 2, 512, 64 * 40 - 5, 64, 64, 24, True),
+    ("split-b128", 3, 128 * 4 - 3, 128 * 30 - 5, 128, 128, 16, True),
+    ("rotated", 2, 64 * 196 - 3, 64 * 1027 - 7, 128, 64, 51, True),
+    ("rotated-d64", 1, 128 * 157 - 3, 128 * 1272 - 7, 64, 128, 63, True),
+]
+
+
+@pytest.mark.parametrize("name,heads,lq,lk,d,b,n,split", INVALID_LIST_CASES, ids=[c[0] for c in INVALID_LIST_CASES])
+def test_empty_and_invalid_list_entries(gpu_lib, name, heads, lq, lk, d, b, n, split):
     """Empty rows give O = 0, lse = -inf; out-of-range entries of an ascending list
     are skipped; counts clamp to the stride."""
     import torch
 
-    w = ATTN_CASES[0][1]
-    _say(f"[empty/invalid lists] split={split}")
-    qb_, kb_, vb_ = generate(w)
-    q, k, v = to_dev(qb_), to_dev(kb_), to_dev(vb_)
-    n_q, n_k = -(-w.lq // w.block), -(-w.lk // w.block)
-    stride = 4
-    num = torch.zeros((1, w.heads, n_q), dtype=torch.int32)
-    idx = torch.zeros((1, w.heads, n_q, stride), dtype=torch.int32)
-    lists_ref = [[[] for _ in range(n_q)] for _ in range(w.heads)]
-    for h in range(w.heads):
-        for i in range(n_q):
-            if i % 3 == 0:
-                continue  # empty
-            if i % 3 == 1:
-                num[0, h, i] = 4
-                idx[0, h, i] = torch.tensor([-3, 1, 4, n_k + 5])
-                lists_ref[h][i] = [1, 4]
-            else:
-                num[0, h, i] = 99  # clamped to the stride (4)
-                idx[0, h, i] = torch.tensor([0, 2, 7, n_k - 1])
-                lists_ref[h][i] = [0, 2, 7, n_k - 1]
-    o, lse = gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num.cuda(), idx.cuda(), w.block, split=split)
+    _say(f"[empty/invalid lists] {name}: H={heads} Lq={lq} Lk={lk} D={d} b={b} stride={n}")
+    p = attn_plan(gpu_lib, 1, heads, lq, lk, d, b, n, split)
+    assert (p.ranges > 1, p.rotation > 0) == (split, name.startswith("rotated"))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(89)
+    q, k, v = (torch.randn(1, heads, l, d, generator=g, device="cuda").to(torch.bfloat16) for l in (lq, lk, lk))
+    n_q, n_k = -(-lq // b), -(-lk // b)
+    idx = torch.rand(1, heads, n_q, n_k, generator=g, device="cuda").topk(n, dim=-1).indices.sort(dim=-1).values
+    num = torch.full((1, heads, n_q), n, dtype=torch.int32)
+    num[:, :, ::4] = 0        # empty
+    num[:, :, 2::4] = n + 95  # clamped to the stride
+    idx[:, :, 1::4, 0] = -3   # an entry before the first block and one past the last
+    idx[:, :, 1::4, -1] = n_k + 5
+    if n > 8:
+        idx[:, :, 3::4, :2] = torch.tensor([-(1 << 31), -1], device="cuda")
+        idx[:, :, 3::4, -3:] = torch.tensor([n_k, n_k + 1, (1 << 31) - 1], device="cuda")
+    o, lse = gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num.cuda(), idx.to(torch.int32), b, split=split)
     torch.cuda.synchronize()
-    refs = [O.sparse_attention(bf16_to_f64(qb_[0, h]), bf16_to_f64(kb_[0, h]), bf16_to_f64(vb_[0, h]),
-                               lists_ref[h], w.block) for h in range(w.heads)]
-    og = bf16_tensor_to_f64(o)
-    lg = lse.cpu().numpy().astype(np.float64)
-    check_output(og, np.stack([r[0] for r in refs])[None], lg, np.stack([r[1] for r in refs])[None], what="lists")
-    assert (og[0, :, : w.block] == 0).all() and np.isneginf(lg[0, :, : w.block]).all()
+    empty = (torch.arange(lq) // b) % 4 == 0
+    assert (o[0][:, empty] == 0).all() and torch.isneginf(lse[0][:, empty]).all()
+    for h in range(heads):
+        kh, vh = bf16_tensor_to_f64(k[0, h]), bf16_tensor_to_f64(v[0, h])
+        for i in sorted({0, 1, 2, 3, n_q // 2, n_q // 2 + 1, n_q - 3, n_q - 2, n_q - 1}):
+            t = slice(i * b, min((i + 1) * b, lq))
+            row = [j for j in idx[0, h, i].tolist() if 0 <= j < n_k] if i % 4 else []
+            o_ref, l_ref = O.sparse_attention(bf16_tensor_to_f64(q[0, h, t]), kh, vh, [row], b)
+            check_output(bf16_tensor_to_f64(o[0, h, t])[None], o_ref[None],
+                         lse[0, h, t].cpu().numpy().astype(np.float64)[None], l_ref[None], what=f"head {h} block {i}")
 
 
 def test_split_agrees_with_single_pass(gpu_lib):
@@ -620,6 +649,7 @@ def test_split_agrees_with_single_pass(gpu_lib):
     qb_, kb_, vb_ = generate(w)
     q, k, v = to_dev(qb_), to_dev(kb_), to_dev(vb_)
     num, idx = gpu_lib.sparstar_score_blocks(q, k, w.block, 0.3, keep_for(gpu_lib, w)[0])
+    _assert_splits(gpu_lib, w, True, idx.shape[-1])
     o1, l1 = gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, w.block, split=True)
     o2, l2 = gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, w.block, split=False)
     torch.cuda.synchronize()
@@ -709,12 +739,11 @@ def _group_offsets(n_groups: int) -> np.ndarray:
 def test_running_max_jumps(gpu_lib, block, split):
     """Logits that rise along every list by a few, by tens and, once, by 150
     binades (Eq. 7's softmax over them).  The kernel forms P against its
-    running max and moves that max only when a 32-key sub-tile's P could pass
-    2^8: small rises stay on the fast path with p up to 2^8, larger ones take
-    the exact path (a power-of-two rescale of O and both row sums, and at
-    b = 128 of the bf16 P of the step's first sub-tile when its second one
-    rises), and the 150-binade jump drops the old terms.  O and lse must match
-    the oracle as on ordinary inputs."""
+    running max and moves that max only when a 32-key tile's P could pass 2^8:
+    small rises stay on the fast path with p up to 2^8, larger ones take the
+    exact path (a power-of-two rescale of O, which holds the tiles before this
+    one, and of both row sums), and the 150-binade jump drops the old terms.  O
+    and lse must match the oracle as on ordinary inputs."""
     w = TINY.with_(name="jumps", head_dim=128, block=block, lq=300, l_ref=1700, l_text=200, heads=2, seed=23)
     rng = np.random.default_rng(29 + block)
 
@@ -799,7 +828,6 @@ def test_attention_writes_only_its_outputs(gpu_lib, dense, split):
 
     w = ATTN_CASES[1][1]
     _say(f"[guard] attention dense={dense} split={split}")
-    _assert_splits(gpu_lib, w, split)
     qb_, kb_, vb_ = generate(w)
     q, k, v = to_dev(qb_), to_dev(kb_), to_dev(vb_)
     n_q = -(-w.lq // w.block)
@@ -813,6 +841,7 @@ def test_attention_writes_only_its_outputs(gpu_lib, dense, split):
     else:
         num, idx = lists_to_device([lists_h], n_q)
         gpu_lib.sparstar_sparse_attn_fwd(q, k, v, num, idx, w.block, out=o, lse=lse, split=split)
+    _assert_splits(gpu_lib, w, split, 0 if dense else idx.shape[-1])
     torch.cuda.synchronize()
     assert _guards_intact(obuf, no), "O: a write outside the output"
     assert _guards_intact(lbuf, nl), "lse: a write outside the output"
