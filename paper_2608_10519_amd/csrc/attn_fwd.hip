@@ -148,11 +148,6 @@ __device__ __forceinline__ s16x4 lds_read_tr(const uint16_t* p) {
       (__attribute__((address_space(3))) s16x4*)(const_cast<uint16_t*>(p)));
 }
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
-  // raw (stride 0) buffer; reads past `bytes` return zeros
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
-}
-
 // Buffer descriptor as four dwords (raw buffer, stride 0, `bytes` records):
 // the form the inline-asm direct-to-LDS load takes.
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -284,20 +279,20 @@ void attn_fwd_kernel(AttnArgs a) {
     pos_lo = blk_lo;
     cnt = blk_hi - blk_lo;
   } else {
-    int blk_st = blk_lo;
-    if (a.rotation > 0) {
-      const uint32_t phase = gi % (uint32_t)a.rotation;
-      blk_st += (int)((int64_t)phase * (blk_hi - blk_lo) / a.rotation);
-    }
     const int64_t r = bh * a.n_q + qg;
     int nblk = a.kv_num_blocks[r];
     nblk = nblk < 0 ? 0 : (nblk > a.stride ? a.stride : nblk);
     list = a.kv_indices + r * a.stride;
-    if (!SPLIT && a.rotation == 0) {
+    if constexpr (!SPLIT) {
       // the whole list from its head: nothing to look for
       pos_lo = 0;
       cnt = __builtin_amdgcn_readfirstlane(nblk);
     } else {
+      int blk_st = blk_lo;
+      if (a.rotation > 0) {
+        const uint32_t phase = gi % (uint32_t)a.rotation;
+        blk_st += (int)((int64_t)phase * (blk_hi - blk_lo) / a.rotation);
+      }
       // 64 x U entries per pass, all loads independent (one memory latency per
       // pass); the counts come from ballots, so they are wave-uniform at once
       constexpr int U = 12;

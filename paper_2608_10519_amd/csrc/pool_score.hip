@@ -223,7 +223,6 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a, int run) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const u32x4 eq = *reinterpret_cast<const u32x4*>(qe + wq * 32 + 8 * g + 4 * h);
-        
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if (irow + 8 * g + e < a.n_q)
