@@ -5,14 +5,14 @@
 // call, whose rows all see the same keys, takes 128 rows whatever the block
 // size, so that each K/V byte loaded feeds twice (b = 64) the queries.  A
 // work-group has one wavefront per 32-row query slice, and every wave takes the
-// whole of each 32-key tile, so no key is ever split between waves and a row's
-// result does not depend on how many waves share its tiles.  Two waves per SIMD
-// at D = 128 (under 256 VGPRs), three at D = 64 (under 168).
+// whole of each tile (32 keys at D = 128, 64 at D = 64: 8 KB of K and of V), so
+// no key is ever split between waves and a row's result does not depend on how
+// many waves share its tiles.  Two waves per SIMD (under 256 VGPRs).
 //
 // Order of the work (XCDs and L2).  Work-groups go round-robin over the eight
 // XCDs.  The id decodes so that each XCD runs the query groups of one (head, key
-// range) pair after the other.  The work-groups in flight on an XCD (8,192 rows
-// at D = 128) then read the same range of K/V, but those that started earlier
+// range) pair after the other.  The work-groups in flight on an XCD (8,192 rows)
+// then read the same range of K/V, but those that started earlier
 // are further along their lists, so between them they touch all of the range.
 // With several ranges, the i-th work-group of a pair therefore starts its list
 // at the fraction (i mod C) / C of the range and wraps around, C being the
@@ -31,7 +31,7 @@
 //
 // Per tile of the query block's key-block list, a three-stage pipeline: step t
 // runs the scores of tile t + 1, the softmax of tile t and P V of tile t - 1.
-//   * K and V tiles (32 x D) go from global memory straight into LDS
+//   * K and V tiles (8 KB) go from global memory straight into LDS
 //     (buffer_load ... lds, 1 KB per wave instruction, coalesced), with no
 //     VGPR staging.  LDS holds two K tiles and two V tiles; each tile has one
 //     and a half steps to land;
@@ -52,9 +52,9 @@
 //     V[r0 .. r0+3][4 c0 + j]: 4 keys of one d column).
 // None of a step's MFMAs waits for the step's softmax or for an LDS read of the
 // same half: the operands of each half are read during the half before.  Every
-// MFMA is followed by its share of the softmax (at D = 128 one exponential, one
-// FMA, one add and half a pack), which issues under it: a 32x32x16 MFMA takes
-// 32 cycles, an FMA 2.7 and an exponential 8.
+// MFMA is followed by its share of the softmax (one exponential, one FMA, one add
+// and half a pack at D = 128, twice that at D = 64), which issues under it: a
+// 32x32x16 MFMA takes 32 cycles, an FMA 2.7 and an exponential 8.
 // The row sum of the bf16 P is taken by v_mfma_f32_4x4x4_16b_bf16 against ones
 // (each lane's four values summed in 8 cycles).  v_dot2_f32_bf16, which sums
 // two, runs on the matrix pipe as well but holds it for about 20 cycles: eight
@@ -89,11 +89,16 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
-// A 32-key step with two waves per SIMD; 64-key tiles need more than 256 VGPRs in
-// this pipeline.
+// A step is sixteen MFMAs (and two barriers) at either head dim:
+// 32-key tiles at D = 128 (64-key tiles need more than 256 VGPRs in this
+// pipeline), 64-key tiles at D = 64, where 32 keys with three waves per SIMD spend
+// as long on barriers, waits and addresses per 8 MFMAs.  Over 300 shapes at D = 64
+// the best cut takes 4.7% less with 64 keys: 20% less where a CU holds one
+// work-group (dense, 209 queries of 2 heads, 134,070 keys: 0.77 of the time), and
+// up to 10% more on lists of a few blocks that fill the chip many times over.
 template <int D, int BLK, int NWAVES>
 struct AttnCfg {
-  static constexpr int KB = 32;               // keys per K/V tile
+  static constexpr int KB = attn_tile_keys(D);  // keys per K/V tile
   static constexpr int SUB = BLK / KB;        // tiles per key block (list entry)
   static constexpr int NW = NWAVES;           // waves: one per 32-row query slice
   static constexpr int NT = 64 * NW;          // threads
@@ -217,7 +222,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 template <int D, int BLK, int NW, bool DENSE, bool SPLIT>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(attn_waves_per_simd(D), attn_waves_per_simd(D))))
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kAttnWavesPerSimd, kAttnWavesPerSimd)))
 void attn_fwd_kernel(AttnArgs a) {
   using C = AttnCfg<D, BLK, NW>;
   static_assert(DENSE || 32 * NW == BLK, "a sparse work-group is one query block");
@@ -376,9 +381,10 @@ void attn_fwd_kernel(AttnArgs a) {
   // descriptor (records = bytes of the tile that exist), so rows past Lk and
   // the tiles past the end of the list arrive as zeros.  Load i adds 1024 i
   // bytes (RPD rows) to both sides, which moves the K permutation by 4 chunks
+  // (of 16 at D = 128, of 8 at D = 64, where two loads come full circle)
   // and leaves the V permutation unchanged; with the instruction offset taking
-  // the 1024 i, the per-lane offset of load i is kdma ^ 64 i for K and vdma for
-  // V (the identity holds for every configuration built).
+  // the 1024 i, the per-lane offset of load i is kdma ^ (64 i mod 16 CPR) for K
+  // and vdma for V (the identity holds for every configuration built).
   uint32_t kdma, vdma;
   {
     const int row = C::RPD * C::DPW * wave + lane / C::CPR, pos = lane % C::CPR;
@@ -399,7 +405,7 @@ void attn_fwd_kernel(AttnArgs a) {
     const i32x4 rs = raw_rsrc(base + (int64_t)(blk < 0 ? 0 : blk) * C::TILE, tile_bytes(blk));
     uint32_t off[C::DPW];
 #pragma unroll
-    for (int i = 0; i < C::DPW; ++i) off[i] = off0 ^ (step * i);
+    for (int i = 0; i < C::DPW; ++i) off[i] = off0 ^ (step * i % (16 * C::CPR));
     dma_tile<C::DPW>(lds_addr(slot) + (uint32_t)(C::DPW * wave) * 1024u, off, rs);
   };
 

@@ -61,7 +61,7 @@ inline int64_t attn_grid(int64_t pairs, int64_t groups, int bits) {
 // share of the key blocks that a list can name (1 for the dense call).
 //
 // What it counts, on the XCD with the most work-groups:
-//   - tile steps: a work-group walks its share of the list, plus 4.5 steps of
+//   - tile steps: a work-group walks its share of the list, plus some 4 steps of
 //     fixed work and, on sparse lists cut into ranges, the 1.9 standard deviations by
 //     which the longest share exceeds the mean.  A step's time depends on how
 //     many work-groups share the CU (kStepUs, D and waves per work-group); whole
@@ -74,9 +74,10 @@ inline int64_t attn_grid(int64_t pairs, int64_t groups, int bits) {
 //   - the merge of the partial results.
 // The constants are fitted to 1,513 random shapes, each timed at every cut (1 to
 // 200 heads, 64 to 72,000 queries, 1,100 to a million keys, 3% to 95% density
-// and dense, uniform and clustered lists, both head dims and block sizes).  The
+// and dense, uniform and clustered lists, both head dims and block sizes); the
+// step times of D = 64 to 770 more of its own.  The
 // chosen cut is 0.8% slower than the best one on average (15% in one shape of
-// a hundred), and 0.6% on 260 shapes that the fit has not seen.  A count of
+// a hundred), and 0.6% on 260 and 256 shapes that the fits have not seen.  A count of
 // ranges from tile steps and K/V per range alone, of at most 8, lost 13%: it took
 // 257 us for 1,000 queries of one head over 144,000 keys (16 ranges: 150), and
 // two ranges for short lists, where the merge costs more than it saves (7,686
@@ -84,11 +85,11 @@ inline int64_t attn_grid(int64_t pairs, int64_t groups, int bits) {
 inline double attn_time_us(int64_t bh, int64_t lq, int64_t lk, int d, int block, double rho, bool dense, int ranges,
                            bool rotated, int group_rows) {
   // by work-groups per CU, for work-groups of two and of four waves
-  static constexpr double kStepUs128[2][6] = {{.44, .67, .69, .87}, {.48, .76}};
-  static constexpr double kStepUs64[2][6] = {{.39, .48, .56, .62, .80, .85}, {.42, .57, .78}};
+  static constexpr double kStepUs128[2][4] = {{.44, .67, .69, .87}, {.48, .76}};
+  static constexpr double kStepUs64[2][4] = {{.63, .83, .97, 1.07}, {.67, .97}};
   const int waves = group_rows / 32;
   const double* step_us = (d == 64 ? kStepUs64 : kStepUs128)[waves / 4];
-  const int per_cu = 4 * attn_waves_per_simd(d) / waves;
+  const int per_cu = 4 * kAttnWavesPerSimd / waves;
   const double held = 32.0 * per_cu;  // work-groups an XCD holds
   const int64_t groups = (lq + group_rows - 1) / group_rows, pairs = bh * ranges;
   const int bits = attn_spread_bits(pairs, groups, group_rows);
@@ -98,9 +99,9 @@ inline double attn_time_us(int64_t bh, int64_t lq, int64_t lk, int d, int block,
   const double rounds = work_groups / held;
   const double whole = floor(rounds), part = rounds - whole;
 
-  const int sub = block / 32;
+  const double sub = double(block) / attn_tile_keys(d);
   const double list_blocks = rho * double((lk + block - 1) / block) / ranges;
-  const double steps = list_blocks * sub + 4.5;
+  const double steps = list_blocks * sub + (d == 64 ? 3.7 : 4.5);
   const double deviation = sqrt(list_blocks * (1.0 - rho));  // of a share's entries
   const double longest = steps + (ranges > 1 && !dense ? 1.9 * deviation * sub : 0.0);
   double t = 2.3 + whole * steps * step_us[per_cu - 1];
@@ -144,20 +145,20 @@ inline AttnPlan attn_plan(int64_t bh, int64_t lq, int64_t lk, int d, int block, 
       const int64_t g = (lq + rows - 1) / rows;
       if (r > 1 && attn_grid(bh * r, g, attn_spread_bits(bh * r, g, rows)) * 2 * rows >> 32) break;  // launch limit
       // (rotation only matters where the work-groups don't all start at once)
-      const bool rounds = bh * r * g * rows > 32768 * attn_waves_per_simd(d);
+      const bool rounds = bh * r * g * rows > 32768 * kAttnWavesPerSimd;
       for (int rotated = 0; rotated <= (r > 1 && !full && rounds); ++rotated) {
         const double t = attn_time_us(bh, lq, lk, d, block, rho, full, r, rotated, rows);
         if (plan.group_rows == 0 || t < (full && r > plan.ranges ? 1.006 * best : best)) {
           best = plan.group_rows == 0 ? t : fmin(best, t);
           plan.group_rows = rows;
           plan.ranges = r;
-          plan.rotation = rotated ? 32 * 4 * attn_waves_per_simd(d) / (rows / 32) : 0;
+          plan.rotation = rotated ? 32 * 4 * kAttnWavesPerSimd / (rows / 32) : 0;
         }
       }
     }
   if (!dense) plan.group_rows = block;
   const int64_t groups = (lq + plan.group_rows - 1) / plan.group_rows, pairs = bh * plan.ranges;
-  const int64_t held = 32 * 4 * attn_waves_per_simd(d) / (plan.group_rows / 32);  // work-groups an XCD holds
+  const int64_t held = 32 * 4 * kAttnWavesPerSimd / (plan.group_rows / 32);  // work-groups an XCD holds
   if (full && !dense && plan.ranges > 1 && pairs * groups >= 8 * 8 * held) plan.rotation = int(held);
   plan.spread_bits = attn_spread_bits(pairs, groups, plan.group_rows);
   plan.grid = attn_grid(pairs, groups, plan.spread_bits);

@@ -119,8 +119,9 @@ inline size_t attn_partial_o_bytes(int64_t rows, int d) { return (size_t(rows * 
 // Bytes of attention workspace for the key-range split (0 when it is not used).
 size_t attn_workspace_bytes(int64_t bh, int64_t n_q, int64_t n_k, int d, int block);
 
-// Waves per SIMD of the attention kernel (a VGPR budget of 256 and 168).
-constexpr int attn_waves_per_simd(int d) { return d == 64 ? 3 : 2; }
+// The attention kernel's waves per SIMD (a VGPR budget of 256) and keys per tile.
+constexpr int kAttnWavesPerSimd = 2;
+constexpr int attn_tile_keys(int d) { return d == 64 ? 64 : 32; }
 
 // Token-wise top-n mass (the upper bound of the retained-mass analysis) for a
 // few sampled query rows per head.

@@ -854,8 +854,8 @@ def test_attention_writes_only_its_outputs(gpu_lib, dense, split):
 # The cuts of the attention plan: (name, heads, Lq, Lk, D, b, listed blocks,
 # then what the library plans: key ranges, rotated lists, pairs shared between
 # XCDs).  tests/test_attn_plan.py checks the last three without a GPU.  The
-# chip holds 65,536 rows at D = 128, 98,304 at D = 64: many-rounds and
-# shared-units take several rounds in one range.
+# chip holds 65,536 rows: many-rounds and shared-units take several rounds in
+# one range.
 PLAN_CASES = [
     ("one-range", 3, 64 * 5 + 1, 64 * 20 + 3, 128, 64, 4, 1, False, True),
     ("many-rounds", 64, 64 * 128, 64 * 160 + 11, 128, 64, 90, 1, False, False),
@@ -863,12 +863,12 @@ PLAN_CASES = [
     ("two-ranges", 24, 64 * 16, 64 * 172 + 5, 128, 64, 53, 2, False, False),
     ("four-ranges", 2, 128 * 17 - 3, 128 * 18 - 7, 64, 128, 9, 4, False, False),
     ("eight-ranges", 1, 128 * 16 + 1, 128 * 64 + 77, 64, 128, 38, 8, False, False),
-    ("sixteen-d64-b64", 1, 64 * 144 - 3, 64 * 230 - 7, 64, 64, 115, 16, False, True),
-    ("sixteen-d64-b128", 1, 128 * 3 - 3, 128 * 19 - 7, 64, 128, 15, 16, False, False),
+    ("sixteen-d64-b64", 1, 64 * 136 - 3, 64 * 300 - 7, 64, 64, 240, 16, False, True),
+    ("sixteen-d64-b128", 1, 128 * 3 - 3, 128 * 40 - 7, 64, 128, 32, 16, False, False),
     ("sixteen-d128-b64", 1, 64 * 4 - 3, 64 * 90 - 7, 128, 64, 72, 16, False, False),
     ("sixteen-d128-b128", 1, 128 * 3 - 3, 128 * 60 - 7, 128, 128, 50, 16, False, False),
     ("rotated-2", 12, 128 * 50 - 3, 128 * 188 - 7, 128, 128, 37, 2, True, False),
-    ("rotated-4-d64", 8, 64 * 80 - 3, 64 * 2009 - 7, 64, 64, 100, 4, True, False),
+    ("rotated-4-d64", 8, 64 * 80 - 3, 64 * 2009 - 7, 64, 64, 160, 4, True, False),
     ("rotated-4-shared", 2, 64 * 196 - 3, 64 * 1027 - 7, 128, 64, 51, 4, True, True),
     ("rotated-8-shared", 1, 128 * 157 - 3, 128 * 1272 - 7, 64, 128, 63, 8, True, True),
     ("rotated-16", 1, 128 * 68 - 3, 128 * 1098 - 7, 128, 128, 109, 16, True, True),

@@ -41,3 +41,15 @@ def test_short_rows_of_the_mass_kernel_share_a_cu(tmp_path):
                          r"\s+\.name:\s+(\S*topk_mass_kernel\S*)", text, re.S):
         fits.append(min(160 * 1024 // int(m.group(1)), 2048 // int(m.group(2))))
     assert sorted(fits) == [1, 4, 8]
+
+
+def test_attention_steps_hold_sixteen_products(tmp_path):
+    """Between two barriers pairs of the attention loop lie sixteen 32x32x16
+    products at D = 64 as at D = 128 (the loop is written out twice, and the
+    prologue and the last P V hold eight of each): the work that a step's two
+    barriers, waits and address updates are spread over."""
+    text = _compile(tmp_path, "attn_fwd.hip")
+    bodies = {m.group(1): m.group(2) for m in re.finditer(r"^(_ZN8sparstar15attn_fwd\w+):.*?\n(.*?)s_endpgm", text, re.S | re.M)}
+    assert len(bodies) == 24
+    for name, body in bodies.items():
+        assert body.count("v_mfma_f32_32x32x16_bf16") >= 2 * 16 + 16, name
