@@ -62,22 +62,22 @@ inline int64_t attn_grid(int64_t pairs, int64_t groups, int bits) {
 //
 // What it counts, on the XCD with the most work-groups:
 //   - tile steps: a work-group walks its share of the list, plus some 4 steps of
-//     fixed work and, on sparse lists cut into ranges, the 1.9 standard deviations by
+//     fixed work and, on sparse lists cut into ranges, the 1.93 standard deviations by
 //     which the longest share exceeds the mean.  A step's time depends on how
 //     many work-groups share the CU (kStepUs, D and waves per work-group); whole
 //     rounds run full, the last one with what is left of it;
 //   - K/V from beyond the L2: once per round for what the lists cover of the
 //     range, and for every work-group where those in flight are too far apart for
-//     the L2 (3.2 MB of it): by the random spread of their positions in the
-//     range, by a quarter of the range per round that they drift without
-//     rotation, by 6% of it with rotation;
+//     the L2 (1.7 MB of it): by a little of the random spread of their positions
+//     in the range, by a quarter of the range per round that they drift without
+//     rotation, by 9% of it with rotation;
 //   - the merge of the partial results.
-// The constants are fitted to 1,513 random shapes, each timed at every cut (1 to
-// 200 heads, 64 to 72,000 queries, 1,100 to a million keys, 3% to 95% density
-// and dense, uniform and clustered lists, both head dims and block sizes); the
-// step times of D = 64 to 770 more of its own.  The
-// chosen cut is 0.8% slower than the best one on average (15% in one shape of
-// a hundred), and 0.6% on 260 and 256 shapes that the fits have not seen.  A count of
+// The constants are fitted to some 2,000 random shapes, each timed at every cut (1
+// to 200 heads, 64 to 72,000 queries, 1,100 to a million keys, 3% to 95% density
+// and dense, uniform and clustered lists, both head dims and block sizes), and to
+// 68 large ones (8 and 24 heads, 25,920 to 72,000 queries, 10% to 80%, budgets
+// equal and per head).  The chosen cut is 0.8% slower than the best one on average
+// (13% in one shape of a hundred), and on the large ones (6% at most).  A count of
 // ranges from tile steps and K/V per range alone, of at most 8, lost 13%: it took
 // 257 us for 1,000 queries of one head over 144,000 keys (16 ranges: 150), and
 // two ranges for short lists, where the merge costs more than it saves (7,686
@@ -103,20 +103,20 @@ inline double attn_time_us(int64_t bh, int64_t lq, int64_t lk, int d, int block,
   const double list_blocks = rho * double((lk + block - 1) / block) / ranges;
   const double steps = list_blocks * sub + (d == 64 ? 3.7 : 4.5);
   const double deviation = sqrt(list_blocks * (1.0 - rho));  // of a share's entries
-  const double longest = steps + (ranges > 1 && !dense ? 1.9 * deviation * sub : 0.0);
+  const double longest = steps + (ranges > 1 && !dense ? 1.93 * deviation * sub : 0.0);
   double t = 2.3 + whole * steps * step_us[per_cu - 1];
   if (part > 0.0) t += longest * step_us[int(fmax(1.0, ceil(part * per_cu - 1e-9))) - 1];
   else t += (longest - steps) * step_us[per_cu - 1];
 
   const double token_bytes = 4.0 * d, range_bytes = double(lk) * token_bytes / ranges;
-  double apart = 1.3 * deviation / rho * block * token_bytes;
-  if (!dense && rounds > 1.0) apart += (rotated ? 0.064 : 0.25 * fmin(1.0, rounds - 1.0)) * range_bytes;
+  double apart = 0.12 * deviation / rho * block * token_bytes;
+  if (!dense && rounds > 1.0) apart += (rotated ? 0.09 : 0.25 * fmin(1.0, rounds - 1.0)) * range_bytes;
   apart = fmin(apart, range_bytes);
-  const double miss = apart > 3.2e6 ? 1.0 - 3.2e6 / apart : 0.0;
+  const double miss = apart > 1.7e6 ? 1.0 - 1.7e6 / apart : 0.0;
   const double covered = dense ? 1.0 : 1.0 - pow(1.0 - rho, fmin(unit_groups, held));
   const double every = work_groups * list_blocks * block * token_bytes;
   const double once = fmin(every, units * fmax(1.0, unit_groups / held) * range_bytes * covered);
-  t += (once * (1.0 - miss) + every * miss) / 9e6;
+  t += (once * (1.0 - miss) + every * miss) / 4.7e6;
   if (ranges > 1)
     t += 3.7 + 0.25 * ranges * block * d / 8192.0 + double(bh) * double(lq) * ranges * token_bytes / 6.3e6;
   return t;

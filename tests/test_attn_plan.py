@@ -4,7 +4,7 @@ import pytest
 
 from paper_2608_10519_amd import sparstar as S
 from tests.helpers import attn_plan
-from tests.test_gpu_parity import PLAN_CASES
+from tests.test_gpu_parity import INVALID_LIST_CASES, PLAN_CASES
 
 
 @pytest.fixture(scope="module")
@@ -75,6 +75,13 @@ def test_plans_of_the_gpu_cases(lib, case):
     assert (p.ranges, p.rotation > 0, p.spread_bits > 0) == (ranges, rotated, shared)
 
 
+@pytest.mark.parametrize("case", INVALID_LIST_CASES, ids=[c[0] for c in INVALID_LIST_CASES])
+def test_plans_of_the_gpu_cases_with_invalid_entries(lib, case):
+    name, heads, lq, lk, d, b, n, split = case
+    p = attn_plan(lib, 1, heads, lq, lk, d, b, n, split)
+    assert (p.ranges > 1, p.rotation > 0) == (split, name.startswith("rotated"))
+
+
 @pytest.mark.parametrize("bh,lq,lk,d,b,stride", [
     (1, 1000, 144_000, 128, 64, 0), (2, 465, 55_727, 64, 64, 0), (2, 199, 57_052, 128, 128, 0),
     (1, 545, 46_955, 64, 128, 143), (2, 170, 189_379, 128, 128, 635), (1, 79, 34_864, 128, 64, 362)])
@@ -104,3 +111,11 @@ def test_rows_of_full_width_are_rotated(lib, lq, lk, rotated):
         p = attn_plan(lib, 1, 24, lq, lk, 128, 64, stride, True)
         assert p.ranges > 1 and (p.rotation > 0) == rotated
     assert attn_plan(lib, 1, 24, lq, lk, 128, 64, 0, True).rotation == 0  # the dense call is not
+
+
+@pytest.mark.parametrize("heads", [24, 8])
+@pytest.mark.parametrize("stride", [1133, 1693, 1806])
+def test_large_calls_with_long_lists_keep_their_ranges_in_the_l2(lib, heads, stride):
+    """Half of 2,258 key blocks and more: two rotated ranges of 37 MB of K/V lose the L2."""
+    p = attn_plan(lib, 1, heads, 72_000, 144_512, 128, 64, stride, True)
+    assert p.ranges in (4, 8) and p.rotation > 0

@@ -599,8 +599,8 @@ INVALID_LIST_CASES = [
     ("onepass", 2, 512, 64 * 18, 64, 64, 4, False),
     ("split", 2, 512, 64 * 40 - 5, 64, 64, 24, True),
     ("split-b128", 3, 128 * 4 - 3, 128 * 30 - 5, 128, 128, 16, True),
-    ("rotated", 2, 64 * 196 - 3, 64 * 1027 - 7, 128, 64, 51, True),
-    ("rotated-d64", 1, 128 * 157 - 3, 128 * 1272 - 7, 64, 128, 63, True),
+    ("rotated", 5, 64 * 105 - 3, 64 * 766 - 7, 128, 64, 76, True),
+    ("rotated-d64", 4, 128 * 73 - 3, 128 * 766 - 7, 64, 128, 76, True),
 ]
 
 
@@ -867,11 +867,11 @@ PLAN_CASES = [
     ("sixteen-d64-b128", 1, 128 * 3 - 3, 128 * 40 - 7, 64, 128, 32, 16, False, False),
     ("sixteen-d128-b64", 1, 64 * 4 - 3, 64 * 90 - 7, 128, 64, 72, 16, False, False),
     ("sixteen-d128-b128", 1, 128 * 3 - 3, 128 * 60 - 7, 128, 128, 50, 16, False, False),
-    ("rotated-2", 12, 128 * 50 - 3, 128 * 188 - 7, 128, 128, 37, 2, True, False),
+    ("rotated-2", 16, 128 * 40 - 3, 128 * 192 - 7, 128, 128, 48, 2, True, False),
     ("rotated-4-d64", 8, 64 * 80 - 3, 64 * 2009 - 7, 64, 64, 160, 4, True, False),
-    ("rotated-4-shared", 2, 64 * 196 - 3, 64 * 1027 - 7, 128, 64, 51, 4, True, True),
-    ("rotated-8-shared", 1, 128 * 157 - 3, 128 * 1272 - 7, 64, 128, 63, 8, True, True),
-    ("rotated-16", 1, 128 * 68 - 3, 128 * 1098 - 7, 128, 128, 109, 16, True, True),
+    ("rotated-4-shared", 5, 64 * 105 - 3, 64 * 766 - 7, 128, 64, 76, 4, True, True),
+    ("rotated-8-shared", 2, 128 * 73 - 3, 128 * 2204 - 7, 64, 128, 220, 8, True, True),
+    ("rotated-16", 1, 128 * 73 - 3, 128 * 2204 - 7, 128, 128, 551, 16, True, True),
 ]
 
 
