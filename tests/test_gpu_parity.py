@@ -880,8 +880,8 @@ def test_plan_cuts_match_oracle(gpu_lib, name, heads, lq, lk, d, b, n):
     """Every cut of the attention call (key ranges, rotated lists) on random
     lists, some of them shorter (one empty), with the partial last block in half
     of them: sampled query blocks against the oracle; the single pass and, with
-    the same lists in a kv_stride that could hold every block (planned as a
-    full list, never rotated), against the same bounds."""
+    the same lists in a kv_stride that could hold every block (the ranges of a
+    full list), against the same bounds."""
     import torch
 
     _say(f"[plan] {name}: H={heads} Lq={lq} Lk={lk} D={d} b={b} n={n}")
